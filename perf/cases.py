@@ -127,7 +127,8 @@ def _cu(lens) -> np.ndarray:
     return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
 
 
-def prepare(case: dict, seed: int) -> dict:
+def _inputs(case: dict, seed: int) -> dict:
+    """The tensors that a call reads, from the seed alone."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
     H, D = case["heads"], case["head_dim"]
 
@@ -135,30 +136,34 @@ def prepare(case: dict, seed: int) -> dict:
         x = torch.randn(shape, device="cuda", generator=gen)
         return (x if scale is None else x * scale).to(torch.bfloat16)
 
-    st = dict(case, stream=torch.cuda.current_stream().cuda_stream, ctx=_context(case.get("splits", 1)))
     if case["op"] == "merge":
         T, P = case["rows"], case["parts"]
-        st["o_parts"] = [noise(T, H, D) for _ in range(P)]
         # log-sum-exp of a few thousand keys each: a common level of its own per part and row noise around it
-        st["lse_parts"] = [8.0 + torch.randn((T, H), device="cuda", generator=gen) for _ in range(P)]
-        st["out"], st["lse"] = torch.empty_like(st["o_parts"][0]), torch.empty_like(st["lse_parts"][0])
-        return st
+        return dict(o_parts=[noise(T, H, D) for _ in range(P)],
+                    lse_parts=[8.0 + torch.randn((T, H), device="cuda", generator=gen) for _ in range(P)])
     if case["op"] == "exchange":
         n, p = case["rows"], case["degree"]
-        st["x"] = noise(n, H, D)
-        st["received"] = noise(p, n, H // p, D)
-        st["send"], st["y"] = torch.empty_like(st["received"]), torch.empty_like(st["x"])
-        return st
+        return dict(x=noise(n, H, D), received=noise(p, n, H // p, D))
     q_lens = _lens(case["q_lens"])
     k_lens = _lens(case["k_lens"]) if case["op"] == "cross" else q_lens
     # N(0, 1), or with a factor of 0.5 to 2 per head, which makes the logits of some heads peaky
     scale = 0.5 + 1.5 * torch.rand((H, 1), device="cuda", generator=gen) if case["head_scale"] else None
-    st["q"] = noise(sum(q_lens), H, D, scale=scale)
-    st["k"], st["v"] = (noise(sum(k_lens), H, D, scale=scale) for _ in range(2))
-    st["cu_q"], st["cu_k"] = _cu(q_lens), _cu(k_lens)
-    st["scale"] = 1.0 / math.sqrt(D)
-    st["out"] = torch.empty_like(st["q"])
-    st["lse"] = torch.empty((sum(q_lens), H), device="cuda") if case["entry"] == "lse" else None
+    q = noise(sum(q_lens), H, D, scale=scale)
+    k, v = (noise(sum(k_lens), H, D, scale=scale) for _ in range(2))
+    return dict(q=q, k=k, v=v, cu_q=_cu(q_lens), cu_k=_cu(k_lens), scale=1.0 / math.sqrt(D))
+
+
+def prepare(case: dict, seed: int) -> dict:
+    st = dict(case, stream=torch.cuda.current_stream().cuda_stream, ctx=_context(case.get("splits", 1)))
+    st.update(_inputs(case, seed))
+    H = case["heads"]
+    if case["op"] == "merge":
+        st["out"], st["lse"] = torch.empty_like(st["o_parts"][0]), torch.empty_like(st["lse_parts"][0])
+    elif case["op"] == "exchange":
+        st["send"], st["y"] = torch.empty_like(st["received"]), torch.empty_like(st["x"])
+    else:
+        st["out"] = torch.empty_like(st["q"])
+        st["lse"] = torch.empty((st["q"].shape[0], H), device="cuda") if case["entry"] == "lse" else None
     return st
 
 
@@ -181,6 +186,38 @@ def run(st: dict):
     else:
         da.dit_attn_varlen_fwd(ctx, q, k, v, st["cu_q"], H, D, st["scale"], out, stream)
     return out if st["lse"] is None else (out, st["lse"])
+
+
+def exact(case: dict, seed: int):
+    """What `run` returns, in 64 bits from the definitions."""
+    x = _inputs(case, seed)
+    if case["op"] == "exchange":
+        n, H, D, p = case["rows"], case["heads"], case["head_dim"], case["degree"]
+        return (x["x"].view(n, p, H // p, D).transpose(0, 1).contiguous(),
+                x["received"].transpose(0, 1).reshape(n, H, D))
+    if case["op"] == "merge":
+        lse = torch.stack(x["lse_parts"]).double()
+        total = torch.logsumexp(lse, 0)
+        out = torch.zeros(x["o_parts"][0].shape, dtype=torch.float64, device="cuda")
+        for o, l in zip(x["o_parts"], lse):
+            out += torch.exp(l - total)[..., None] * o
+        return out, total
+    q, k, v, cu_q, cu_k = x["q"], x["k"], x["v"], x["cu_q"], x["cu_k"]
+    out = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+    lse = torch.empty(q.shape[:2], dtype=torch.float64, device="cuda")
+    for q0, q1, k0, k1 in zip(cu_q[:-1], cu_q[1:], cu_k[:-1], cu_k[1:]):
+        step = max(1, int(2.5e8 // (k1 - k0)))  # rows at a time: two gigabytes of scores
+        for h in range(case["heads"]):
+            kt, vh = k[k0:k1, h].double().t().contiguous(), v[k0:k1, h].double()
+            for r0 in range(q0, q1, step):
+                r1 = min(q1, r0 + step)
+                s = (q[r0:r1, h].double() @ kt).mul_(x["scale"])
+                m = s.amax(1, keepdim=True)
+                s = s.sub_(m).exp_()
+                total = s.sum(1, keepdim=True)
+                out[r0:r1, h] = (s @ vh) / total
+                lse[r0:r1, h] = (m + total.log())[:, 0]
+    return (out, lse) if case["entry"] == "lse" else out
 
 
 def work(case: dict) -> dict:
