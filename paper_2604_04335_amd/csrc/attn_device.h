@@ -561,15 +561,16 @@ __device__ __forceinline__ void phase_barrier() { asm volatile("s_barrier" ::: "
 // next index only towards the end of the current item (two tiles before it ends): asking earlier hides no more latency
 // and takes an item away from workgroups that become idle before this one gets to it (with one item per workgroup and
 // the request made at the start of an item, the first workgroups to start took two items each and the last none).
-__device__ __forceinline__ uint32_t take_item(const AttnParams& p) { return gridDim.x + atomicAdd(&p.sync[0], 1u); }
-// After the item loop: the last workgroup to get here clears both words for the next launch.
-__device__ __forceinline__ void finish_workgroup(const AttnParams& p) {
-  __threadfence();
-  const uint32_t done = atomicAdd(&p.sync[1], 1u);
-  if (done == gridDim.x - 1) {
-    p.sync[0] = 0u;
-    p.sync[1] = 0u;
-  }
+// One index is asked for per item, n_items in all, so the asker who is answered n_items - 1 is the last of the launch
+// and clears the counter for the next one.  (Counting finished workgroups instead, behind a fence that writes the L2
+// back, cost 3 to 7 us at the end of every launch.)
+// A list with no more items than workgroups is done after one item each: nobody asks.  Both together, before and after,
+// MI355X: 410 rows x 24 heads x D 64: 12.0 -> 8.9 us, 1024 x 24 x 64: 24.2 -> 17.2 us, 2458 x 24 x 128: 77.9 -> 70.2 us.
+__device__ __forceinline__ bool single_round(const AttnParams& p) { return p.n_items <= gridDim.x; }
+__device__ __forceinline__ uint32_t take_item(const AttnParams& p) {
+  const uint32_t taken = atomicAdd(&p.sync[0], 1u);
+  if (taken == p.n_items - 1) __hip_atomic_store(&p.sync[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return gridDim.x + taken;
 }
 
 // Clock sample of a launch: workgroup 0 (persistent, so it lives about as long as the kernel) reads the shader-cycle

@@ -18,11 +18,10 @@ struct AttnParams {
   int64_t part_rows;        // Tq
   float* lse;               // fp32 [T, H] or nullptr: natural-log sum of exp(scale * score) of every (query row, head)
   const WorkItem* items;    // device work-list
-  uint32_t* sync;           // device, 8 words (8-byte aligned): [0] items taken so far, [1] workgroups finished,
-                            // [2..3] shader cycles and [4..5] 100 MHz ticks workgroup 0 of the last launch ran for.
-                            // Words 0 and 1 are zero
-                            // between launches: the last workgroup to finish clears them (so a launch can be
-                            // replayed from a captured graph, and the host keeps no count).
+  uint32_t* sync;           // device, 8 words (8-byte aligned): [0] items asked for so far, [1] unused, [2..3] shader
+                            // cycles and [4..5] 100 MHz ticks workgroup 0 of the last launch ran for.  Word 0 is zero
+                            // between launches: the last workgroup to ask clears it (so a launch can be replayed from
+                            // a captured graph, and the host keeps no count).
   uint32_t n_items;
   int32_t n_heads;
   float c_log2;             // |scale| * log2(e), at least 1e-30: never zero, so that a masked score of -inf times it

@@ -25,13 +25,11 @@ attn_fwd_kernel(AttnParams p) {
 
   // The index of the next item is requested towards the end of an item, into the slot of the other parity; a barrier
   // between that write and the end of the item makes it visible to every wave before it is read.
-  if (tid == 0) s_item[0] = blockIdx.x;
-  wg_barrier();
+  const bool one_round = single_round(p);
+  uint32_t item_idx = blockIdx.x;
   int par = 0;
 
-  for (;;) {
-    const uint32_t item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
-    if (item_idx >= p.n_items) break;
+  while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
     const ItemCtx<T> X = begin_item<T>(p, L, item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;
@@ -57,7 +55,7 @@ attn_fwd_kernel(AttnParams p) {
     int ka[T::NKS], va[T::NDB];  // operand addresses in the buffers of the current tile's parity
     L.operand_addrs((uint32_t)(uintptr_t)smem, (uint32_t)(uintptr_t)smem, ka, va);
 
-    if (nt == 1 && tid == 0) s_item[par] = take_item(p);  // visible after the barrier below
+    if (nt == 1 && tid == 0 && !one_round) s_item[par] = take_item(p);  // visible after the barrier below
     for (int t = 0; t + 1 < nt; ++t) {
       // Tile t has landed (this wave's loads), and after the barrier everyone's; everyone is also done
       // reading the other buffers (tile t-1), so they can be refilled with tile t+1 while tile t is used.
@@ -66,7 +64,7 @@ attn_fwd_kernel(AttnParams p) {
       // The next index is requested here and put into its slot at the end of the tile (visible after the barrier of
       // the last tile): the request takes about a microsecond to come back, which thread 0's wavefront spends on
       // the tile instead of waiting.
-      const bool ask = t + 2 == nt && tid == 0;
+      const bool ask = t + 2 == nt && tid == 0 && !one_round;
       uint32_t next_item = 0;
       if (ask) next_item = take_item(p);
       load_tile(t + 1);
@@ -92,10 +90,11 @@ attn_fwd_kernel(AttnParams p) {
     const uint32_t stage = (uint32_t)(uintptr_t)smem + (L.wave < 2 ? T::K_OFF : T::V_OFF) + (nt & 1) * T::TILE_B +
                            (uint32_t)(L.wave & 1) * (32 * T::ROW_B);
     store_out<T>(p, L, X.it, row_stride_b, X.head_off, X.qrow, X.row_valid, o, l_run, m_ref, stage);
+    if (one_round) break;
     wg_barrier();  // the next item's first loads overwrite the buffers of parity 0
+    item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
   }
   launch_clock_end(p, clock0);
-  if (tid == 0) finish_workgroup(p);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -157,13 +156,11 @@ attn_fwd_pp_kernel(AttnParams p) {
 
   // The index of the next item is requested towards the end of an item, into the slot of the other parity; a barrier
   // between that write and the end of the item makes it visible to every wave before it is read.
-  if (tid == 0) s_item[0] = blockIdx.x;
-  wg_barrier();
+  const bool one_round = single_round(p);
+  uint32_t item_idx = blockIdx.x;
   int par = 0;
 
-  for (;;) {
-    const uint32_t item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
-    if (item_idx >= p.n_items) break;
+  while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
     const ItemCtx<T> X = begin_item<T>(p, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;  // nt: 64-key tiles
@@ -249,6 +246,8 @@ attn_fwd_pp_kernel(AttnParams p) {
       wg_barrier();
       wg_barrier();
       if (group == 0) wg_barrier();
+      if (one_round) break;
+      item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
       continue;
     }
     bf16x8 qf[T::NKS];
@@ -290,13 +289,13 @@ attn_fwd_pp_kernel(AttnParams p) {
     if (group == 1) wait_loads();
     wg_barrier();
 
-    if (npairs == 1 && tid == 0) s_item[par] = take_item(p);  // two barriers follow in the last pair
+    if (npairs == 1 && tid == 0 && !one_round) s_item[par] = take_item(p);  // two barriers follow in the last pair
     for (int t = 0; t + 1 < npairs; ++t) {
       // ---- vector phase: softmax of both tiles of pair t (whole tiles)
       // The next index is requested at the start of this phase and put into its slot at the end (visible after the
       // barriers of the last pair): the request takes about a microsecond, which thread 0's wavefront spends on its
       // softmaxes instead of waiting while seven wavefronts wait for it at the barrier.
-      const bool ask = t + 2 == npairs && tid == 0;
+      const bool ask = t + 2 == npairs && tid == 0 && !one_round;
       uint32_t next_item = 0;
       if (ask) next_item = take_item(p);
       if (group == 1) load_v_pair_all(t + 1);            // read from phase 2t+4 on
@@ -354,9 +353,10 @@ attn_fwd_pp_kernel(AttnParams p) {
       store_out<T>(p, L, X.it, row_stride_b, X.head_off, qrow, row_valid, o, l_run, m_ref, stage);
     }
     if (group == 0) wg_barrier();  // group 0 idles (after its stores) while group 1 runs its last matrix phase
+    if (one_round) break;
+    item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
   }
   launch_clock_end(p, clock0);
-  if (tid == 0) finish_workgroup(p);
 }
 
 // The LDS limit of a kernel is set once per device (its first use there also loads the kernel's code).

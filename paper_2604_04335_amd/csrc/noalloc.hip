@@ -8,7 +8,7 @@
 //
 // Every call on a GPU shares that GPU's copy of the array: calls that overlap on one GPU (two streams, two contexts,
 // two threads) race.  The array keeps the last call's contents; the plan kernel rewrites every item that the next
-// launch reads and clears the two work counters, so nothing is assumed about what an earlier call left.
+// launch reads and clears the work counter, so nothing is assumed about what an earlier call left.
 #include "noalloc.h"
 
 namespace dit {
@@ -37,7 +37,6 @@ __global__ void __launch_bounds__(256) noalloc_plan_kernel(PackArg pack, int32_t
   __shared__ uint32_t first[kNoAllocMaxSeqs + 1];  // index of the first item of the i-th sequence in list order
   if (threadIdx.x == 0) {
     sync[0] = 0u;
-    sync[1] = 0u;
     int32_t n = 0;
     for (int32_t i = 0; i < pack.n_seqs; ++i) {  // stable insertion sort by descending length, empty sequences dropped
       const int32_t len = pack.cu[i + 1] - pack.cu[i];
