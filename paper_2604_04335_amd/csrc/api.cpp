@@ -539,7 +539,7 @@ static int sp_layout(dit_attn_ctx* ctx, bool pack, const void* src, void* dst, i
   DeviceGuard guard;
   hipError_t e = guard.enter(ctx->device);
   if (e != hipSuccess) return fail_hip(ctx, e, "hipSetDevice");
-  e = dit::sp_layout_launch(pack, src, dst, n_rows, n_heads, head_dim, sp_degree, ctx->n_cus, static_cast<hipStream_t>(stream));
+  e = dit::sp_layout_launch(pack, src, dst, n_rows, n_heads, head_dim, sp_degree, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail_hip(ctx, e, "layout kernel launch");
   return DIT_ATTN_OK;
 }

@@ -126,3 +126,29 @@ def test_gpu_layout_errors():
         assert e.value.code == -1
     finally:
         da.dit_attn_destroy(ctx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,n,H,D", [(1, 1, 1, 64), (1, 31, 1, 64), (5, 7, 5, 64), (40, 13, 40, 128), (2, 16383, 40, 128), (2, 16385, 40, 128)])
+def test_gpu_layout_edges(p, n, H, D):
+    """One chunk run of eight, groups smaller than and not a multiple of a workgroup, one head per group, and either side of
+    the 160 MiB line from which the source is read with streaming loads: every bit, both directions."""
+    import torch
+    import paper_2604_04335_amd as da
+    print(f"layout edges: p={p} n={n} H={H} D={D}", flush=True)
+    ctx = da.dit_attn_create(0)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(p + n)
+        x = torch.randint(-32768, 32767, (n, H, D), dtype=torch.int16, device="cuda", generator=gen)
+        buf = torch.full((x.numel() + 128,), 0x7FC1, dtype=torch.int16, device="cuda")
+        back = torch.full((x.numel() + 128,), 0x7FC1, dtype=torch.int16, device="cuda")
+        st = torch.cuda.current_stream().cuda_stream
+        da.dit_attn_sp_pack_heads(ctx, x, buf[64:-64], n, H, D, p, st)
+        da.dit_attn_sp_unpack_heads(ctx, buf[64:-64], back[64:-64], n, H, D, p, st)
+        torch.cuda.synchronize()
+        assert torch.equal(buf[64:-64].view(p, n, H // p, D), x.view(n, p, H // p, D).transpose(0, 1))
+        assert torch.equal(back[64:-64].view(n, H, D), x)
+        for b in (buf, back):
+            assert bool((b[:64] == 0x7FC1).all()) and bool((b[-64:] == 0x7FC1).all())
+    finally:
+        da.dit_attn_destroy(ctx)
