@@ -4,7 +4,7 @@
 // sequence, the ring half of the unified sequence parallelism of paper Section 5, hands every GPU one key block per
 // step; split-KV does the same inside one GPU).  With lse = ln sum_p exp(lse_p):
 //     O = sum_p exp(lse_p - lse) O_p.
-// Elementwise and HBM bound: P * (T*H*D*2 + T*H*4) bytes in, T*H*D*2 + T*H*4 out; one thread per 16 output bytes.
+// Elementwise and HBM bound: P * (T*H*D*2 + T*H*4) bytes in, T*H*D*2 + T*H*4 out; a thread works on 16-byte chunks.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,96 +23,115 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));  // round to nearest even
 }
 
-template <int P, bool F32>
+// U chunks per thread, 256 apart, all their loads issued before the first is used.  SHIFT: log2 of the chunks of a (row,
+// head).  STREAM: the parts are read with streaming loads.
+// Four bf16 parts on 49178 rows x 24 heads x 128 (1.5 GB in all), MI355X, us: one chunk per thread and ordinary accesses
+// 281 (5.4 TB/s); streaming loads and stores 261, with two chunks per thread 254, with four 247 (6.2 TB/s).
+template <int P, bool F32, int U, int SHIFT, bool STREAM>
 __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;  // 16-byte chunk of the output
-  if (e >= p.n_chunks) return;
-  const int64_t rh = e / p.chunks_per_row;                    // (row, head)
-  float l[P], m = -__builtin_inff();
+  static_assert(!F32 || U == 1, "fp32 parts: one chunk per thread");
+  const int64_t e0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;  // 16-byte chunk of the output
+  float l[U][P];
+  u32x4 x[U][P];
 #pragma unroll
-  for (int i = 0; i < P; ++i) {
-    l[i] = p.lse[i][rh];
-    m = __builtin_fmaxf(m, l[i]);
-  }
-  const float m_safe = m == -__builtin_inff() ? 0.f : m;
-  float w[P], tot = 0.f;
+  for (int j = 0; j < U; ++j) {
+    const int64_t e = e0 + j * 256;
+    if (e >= p.n_chunks) continue;
 #pragma unroll
-  for (int i = 0; i < P; ++i) {
-    w[i] = __expf(l[i] - m_safe);  // exp(-inf) = 0: a part without keys has no weight
-    tot += w[i];
-  }
-  const float inv = tot > 0.f ? 1.0f / tot : 0.f;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < P; ++i) {
-    const float wi = w[i] * inv;
-    float xv[8];
-    if (F32) {
-      typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-      const f32x4* src = reinterpret_cast<const f32x4*>(p.o[i]) + 2 * e;
-      const f32x4 x0 = src[0], x1 = src[1];
-      xv[0] = x0[0]; xv[1] = x0[1]; xv[2] = x0[2]; xv[3] = x0[3];
-      xv[4] = x1[0]; xv[5] = x1[1]; xv[6] = x1[2]; xv[7] = x1[3];
-    } else {
-      const u32x4 x = reinterpret_cast<const u32x4*>(p.o[i])[e];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        xv[2 * j] = bf16_lo(x[j]);
-        xv[2 * j + 1] = bf16_hi(x[j]);
+    for (int i = 0; i < P; ++i) {
+      l[j][i] = p.lse[i][e >> SHIFT];
+      if constexpr (!F32) {
+        const u32x4* src = reinterpret_cast<const u32x4*>(p.o[i]) + e;
+        x[j][i] = STREAM ? __builtin_nontemporal_load(src) : *src;
       }
     }
-    // a weight of exactly 0 must also silence a non-finite value of a part that had no keys
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += wi == 0.f ? 0.f : wi * xv[j];
   }
-  u32x4 y;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) y[j] = pack2(acc[2 * j], acc[2 * j + 1]);
-  reinterpret_cast<u32x4*>(p.out)[e] = y;
-  if (p.lse_out != nullptr && e % p.chunks_per_row == 0) p.lse_out[rh] = tot > 0.f ? m_safe + __logf(tot) : -__builtin_inff();
+  for (int j = 0; j < U; ++j) {
+    const int64_t e = e0 + j * 256;
+    if (e >= p.n_chunks) break;
+    const int64_t rh = e >> SHIFT;  // (row, head)
+    float m = -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < P; ++i) m = __builtin_fmaxf(m, l[j][i]);
+    const float m_safe = m == -__builtin_inff() ? 0.f : m;
+    float w[P], tot = 0.f;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      w[i] = __expf(l[j][i] - m_safe);  // exp(-inf) = 0: a part without keys has no weight
+      tot += w[i];
+    }
+    const float inv = tot > 0.f ? 1.0f / tot : 0.f;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const float wi = w[i] * inv;
+      float xv[8];
+      if constexpr (F32) {
+        typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+        const f32x4* src = reinterpret_cast<const f32x4*>(p.o[i]) + 2 * e;
+        const f32x4 x0 = src[0], x1 = src[1];
+        xv[0] = x0[0]; xv[1] = x0[1]; xv[2] = x0[2]; xv[3] = x0[3];
+        xv[4] = x1[0]; xv[5] = x1[1]; xv[6] = x1[2]; xv[7] = x1[3];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          xv[2 * k] = bf16_lo(x[j][i][k]);
+          xv[2 * k + 1] = bf16_hi(x[j][i][k]);
+        }
+      }
+      // a weight of exactly 0 must also silence a non-finite value of a part that had no keys
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += wi == 0.f ? 0.f : wi * xv[k];
+    }
+    u32x4 y;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y[k] = pack2(acc[2 * k], acc[2 * k + 1]);
+    __builtin_nontemporal_store(y, reinterpret_cast<u32x4*>(p.out) + e);
+    if (p.lse_out != nullptr && (e & ((1 << SHIFT) - 1)) == 0) p.lse_out[rh] = tot > 0.f ? m_safe + __logf(tot) : -__builtin_inff();
+  }
+}
+
+// Parts of this many bytes and more in all are read with streaming loads.  Below, the 256 MB memory-side cache still
+// holds much of what the kernels before wrote: four parts of 295 MB in all 56 us with ordinary loads and 61 us with
+// streaming ones, of 147 MB 27.5 and 30; above, of 590 MB 132 and 120, of 1.2 GB 272 and 247.
+constexpr int64_t kStreamBytes = 400ll << 20;
+
+template <int P, bool F32, int U, int SHIFT, bool STREAM>
+static hipError_t launch(const MergeParams& p, hipStream_t stream) {
+  const int64_t blocks = (p.n_chunks + 256 * U - 1) / (256 * U);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((merge_kernel<P, F32, U, SHIFT, STREAM>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <int P, int SHIFT>
+static hipError_t launch_parts(const MergeParams& p, hipStream_t stream) {
+  if (p.in_f32) return launch<P, true, 1, SHIFT, false>(p, stream);
+  if (P * p.n_chunks * 16 < kStreamBytes) return launch<P, false, 2, SHIFT, false>(p, stream);
+  return launch<P, false, P <= 4 ? 4 : 2, SHIFT, true>(p, stream);  // 64 registers of loads in flight
+}
+
+template <int P>
+static hipError_t launch_rows(const MergeParams& p, hipStream_t stream) {
+  if (p.chunks_per_row == 8) return launch_parts<P, 3>(p, stream);
+  if (p.chunks_per_row == 16) return launch_parts<P, 4>(p, stream);
+  return hipErrorInvalidValue;
 }
 
 hipError_t merge_launch(const MergeParams& p, int n_parts, hipStream_t stream) {
   if (p.n_chunks == 0) return hipSuccess;
-  const int64_t blocks = (p.n_chunks + 255) / 256;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(256);
   switch (n_parts) {
-    case 1:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<1, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<1, false>), grid, block, 0, stream, p);
-      break;
-    case 2:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<2, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<2, false>), grid, block, 0, stream, p);
-      break;
-    case 3:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<3, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<3, false>), grid, block, 0, stream, p);
-      break;
-    case 4:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<4, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<4, false>), grid, block, 0, stream, p);
-      break;
-    case 5:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<5, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<5, false>), grid, block, 0, stream, p);
-      break;
-    case 6:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<6, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<6, false>), grid, block, 0, stream, p);
-      break;
-    case 7:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<7, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<7, false>), grid, block, 0, stream, p);
-      break;
-    case 8:
-      if (p.in_f32) hipLaunchKernelGGL((merge_kernel<8, true>), grid, block, 0, stream, p);
-      else hipLaunchKernelGGL((merge_kernel<8, false>), grid, block, 0, stream, p);
-      break;
+    case 1: return launch_rows<1>(p, stream);
+    case 2: return launch_rows<2>(p, stream);
+    case 3: return launch_rows<3>(p, stream);
+    case 4: return launch_rows<4>(p, stream);
+    case 5: return launch_rows<5>(p, stream);
+    case 6: return launch_rows<6>(p, stream);
+    case 7: return launch_rows<7>(p, stream);
+    case 8: return launch_rows<8>(p, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // Rows [row0, row0 + n_rows) of out (n_rows * row_chunks 16-byte chunks) := 0 and of lse := -inf: query rows of a

@@ -1,0 +1,55 @@
+"""The merge kernel at the edges of its chunks per thread and of the line from which the parts are read with streaming loads."""
+import pytest
+import torch
+
+import paper_2604_04335_amd as da
+
+pytestmark = pytest.mark.gpu
+
+
+def _parts(n_parts, T, H, D, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    o = [torch.randn((T, H, D), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(n_parts)]
+    lse = [8.0 + torch.randn((T, H), device="cuda", generator=gen) for _ in range(n_parts)]
+    lse[0][::3] = float("-inf")
+    return o, lse
+
+
+def _merge(o, lse):
+    T, H, D = o[0].shape
+    ctx = da.dit_attn_create(0)
+    try:
+        buf = torch.full((T * H * D + 128,), 0x7FC1, dtype=torch.int16, device="cuda")
+        out, l = buf[64:-64].view(torch.bfloat16).view(T, H, D), torch.full((T, H), float("nan"), device="cuda")
+        da.dit_attn_merge(ctx, o, lse, T, H, D, out, l, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert bool((buf[:64] == 0x7FC1).all()) and bool((buf[-64:] == 0x7FC1).all())
+        return out, l
+    finally:
+        da.dit_attn_destroy(ctx)
+
+
+@pytest.mark.parametrize("D,T,H", [(64, 1, 1), (64, 63, 1), (64, 65, 1), (128, 31, 1), (128, 33, 1), (128, 64, 1), (128, 21, 3)])
+@pytest.mark.parametrize("n_parts", [2, 4, 8])
+def test_chunks_per_thread(n_parts, D, T, H):
+    """Eight chunks in all up to a few workgroups and a remainder of one row."""
+    print(f"merge edges: parts={n_parts} T={T} H={H} D={D}", flush=True)
+    o, lse = _parts(n_parts, T, H, D, 7 * T + D)
+    out, l = _merge(o, lse)
+    total = torch.logsumexp(torch.stack(lse).double(), 0)
+    ref = sum(torch.exp(x.double() - total)[..., None] * y.double() for x, y in zip(lse, o))
+    # the output's rounding to bf16 (2^-9 relative to the element) and fp32 arithmetic far below it
+    assert bool(((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
+    assert float((l.double() - total).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("n_parts", [4, 5])
+def test_either_side_of_the_streaming_line(n_parts):
+    """400 MiB of parts: the last row count below and the first above give the same bits on the rows they share."""
+    H, D = 24, 128
+    T = -(-(400 << 20) // (n_parts * H * D * 2))
+    print(f"merge streaming line: parts={n_parts} T={T}", flush=True)
+    o, lse = _parts(n_parts, T, H, D, n_parts)
+    above, l_above = _merge(o, lse)
+    below, l_below = _merge([x[:T - 1] for x in o], [x[:T - 1] for x in lse])
+    assert torch.equal(above[:T - 1].view(torch.int16), below.view(torch.int16)) and torch.equal(l_above[:T - 1], l_below)
