@@ -249,6 +249,43 @@ int64_t dit_attn_plan(const int32_t* cu_seqlens, int32_t n_seqs, int32_t n_heads
 
 namespace {
 
+// Split-KV (opt-in): a pack that leaves compute units idle cuts every sequence's keys into chunks of at least eight key
+// tiles, as many as still run in one round, one workgroup per compute unit, and merges the parts.
+// Measured on MI355X, head dimension 128 unless noted, rows x heads: us unsplit / ping-pong kernel (2, 3, 4, 5, 8 chunks) /
+// 128-row kernel (the same):
+//   16384 x 1          284 / 167 131 124 165 134 / 165 161 138 161 147
+//   10000 x 3          183 / 138 172 155 173 176 / 158 170 171 169 193
+//   8192 x 2           145 /  90  74  71  93  84 /  88  86  78  90  88
+//   4951 x 3            88 /  61  50  48  66  62 /  57  57  52  61  63
+//   4096 x 6            80 /  60  83  75  75  87 /  71  78  70  77  89
+//   4096 x 4, D 64      53 /  42  33  34  42  40 /  37  35  34  37  38
+//   3 of 2000, 2 heads  39 /  33  30  28  34  40 /  30  32  30  32  37
+//   2500 x 3            47 /  37  30  30  26  28 /  33  27  27  28  28
+//   1570 x 5            31 /  29  26  27  24  27 /  25  22  24  25  28
+// The ping-pong kernel is ahead where a chunk count fills one round of its items; with under 32 key tiles the shorter
+// items of the 128-row kernel are.  The partial results and their merge cost about 9 us, a key tile 1 us per item: a split
+// has to take at least twelve tiles off every item.
+void choose_split(const dit_attn_ctx* ctx, const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads,
+                  dit::AttnKernel* kernel, int32_t* n_splits) {
+  int64_t rows128 = 0, rows256 = 0, min_tiles = INT64_MAX;  // query tiles of either height
+  for (int32_t i = 0; i < n_seqs; ++i) {
+    const int64_t lq = cu_q[i + 1] - cu_q[i], lk = cu_k[i + 1] - cu_k[i];
+    if (lq == 0 || lk == 0) continue;
+    rows128 += (lq + 127) / 128;
+    rows256 += (lq + 255) / 256;
+    min_tiles = std::min<int64_t>(min_tiles, (lk + 63) / 64);
+  }
+  if (rows128 == 0) return;
+  const dit::AttnKernel split_kernel = ctx->force_kernel >= 0 ? *kernel
+                                       : min_tiles < 32       ? dit::AttnKernel::kIndependent128
+                                                              : dit::AttnKernel::kPingPong256;
+  const int64_t items = (split_kernel == dit::AttnKernel::kIndependent128 ? rows128 : rows256) * n_heads;
+  const int64_t n = std::min<int64_t>({ctx->n_cus / items, ctx->max_splits, min_tiles / 8});
+  if (n < 2 || min_tiles - (min_tiles + n - 1) / n < 12) return;
+  *kernel = split_kernel;
+  *n_splits = static_cast<int32_t>(n);
+}
+
 // cu_k == nullptr: self-attention (keys share the query boundaries).  lse may be nullptr.
 int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, const int32_t* cu_seqlens, const int32_t* cu_k,
             int32_t n_seqs, int32_t n_heads, int32_t head_dim, float scale, void* out, float* lse, void* stream) {
@@ -282,31 +319,10 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   // Plan cache: the same pack comes back for every DiT block of every step.
   CachedPlan* plan = nullptr;
   const size_t cu_n = static_cast<size_t>(n_seqs) + 1;
-  const dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
-                                                        : dit::attn_fwd_select(cu_seqlens, cu_k, n_seqs, n_heads, ctx->n_cus);
-  // Split-KV (opt-in): a pack of the 128-row kernel with fewer items than compute units cuts every sequence's keys into
-  // chunks of at least four key tiles, as many as it takes to reach two items per compute unit, and merges the parts.
+  dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
+                                                  : dit::attn_fwd_select(cu_seqlens, cu_k, n_seqs, n_heads, ctx->n_cus);
   int32_t n_splits = 1;
-  if (ctx->max_splits > 1 && kernel == dit::AttnKernel::kIndependent128) {
-    const int32_t* ck = cu_k ? cu_k : cu_seqlens;
-    int64_t items = 0, min_tiles = INT64_MAX;
-    for (int32_t i = 0; i < n_seqs; ++i) {
-      const int64_t lq = cu_seqlens[i + 1] - cu_seqlens[i], lk = ck[i + 1] - ck[i];
-      if (lq == 0 || lk == 0) continue;
-      items += (lq + 127) / 128 * n_heads;
-      min_tiles = std::min<int64_t>(min_tiles, (lk + 63) / 64);
-    }
-    if (items > 0 && items < ctx->n_cus) {
-      const int64_t want = (2 * static_cast<int64_t>(ctx->n_cus) + items - 1) / items;
-      const int64_t n = std::max<int64_t>(1, std::min<int64_t>({want, ctx->max_splits, min_tiles / 4}));
-      // Measured on MI355X (128-row kernel, one workgroup per compute unit, head dimension 128): an unsplit call takes
-      // about 10 us + 1.1 us per key tile, a call split n ways 37 us (fill and merge launches, fp32 partials, one more
-      // start-up per chunk) + 1.7 / n of the unsplit time.  Split only where that is a gain: from 49 key tiles on for
-      // n = 4, 68 for n = 3, 34 for n = 8.
-      const double t_unsplit = 10.0 + 1.1 * static_cast<double>(min_tiles);
-      if (n > 1 && t_unsplit * (1.0 - 1.7 / static_cast<double>(n)) > 37.0) n_splits = static_cast<int32_t>(n);
-    }
-  }
+  if (ctx->max_splits > 1) choose_split(ctx, cu_seqlens, cu_k ? cu_k : cu_seqlens, n_seqs, n_heads, &kernel, &n_splits);
   for (auto& p : ctx->plans) {
     if (p->n_heads == n_heads && p->head_dim == head_dim && p->kernel == kernel && p->n_splits == n_splits && p->cu.size() == cu_n &&
         p->cu_k.size() == (cu_k ? cu_n : 0) && std::memcmp(p->cu.data(), cu_seqlens, cu_n * sizeof(int32_t)) == 0 &&
