@@ -228,7 +228,7 @@ int64_t dit_attn_plan(const int32_t* cu_seqlens, int32_t n_seqs, int32_t n_heads
   const int rc = check_shape_args(cu_seqlens, n_seqs, n_heads, head_dim, msg);
   if (rc != DIT_ATTN_OK) return rc;
   if (capacity_items > 0 && !items) return DIT_ATTN_ERR_NULL;
-  const dit::AttnKernel kernel = dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, kMi355xComputeUnits);
+  const dit::AttnKernel kernel = dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, head_dim, kMi355xComputeUnits);
   const int bm = dit::attn_fwd_block_m(kernel);
   if (block_m) *block_m = bm;
   std::vector<dit::WorkItem> list;
@@ -320,7 +320,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   CachedPlan* plan = nullptr;
   const size_t cu_n = static_cast<size_t>(n_seqs) + 1;
   dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
-                                                  : dit::attn_fwd_select(cu_seqlens, cu_k, n_seqs, n_heads, ctx->n_cus);
+                                                  : dit::attn_fwd_select(cu_seqlens, cu_k, n_seqs, n_heads, head_dim, ctx->n_cus);
   int32_t n_splits = 1;
   if (ctx->max_splits > 1) choose_split(ctx, cu_seqlens, cu_k ? cu_k : cu_seqlens, n_seqs, n_heads, &kernel, &n_splits);
   for (auto& p : ctx->plans) {
@@ -390,7 +390,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   }
   const uint32_t n_items = static_cast<uint32_t>(plan->host_items.size());
   if (n_items == 0) return DIT_ATTN_OK;
-  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(plan->kernel);
+  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(plan->kernel, head_dim);
   const int grid = static_cast<int>(n_items < max_grid ? n_items : max_grid);
 
   const int64_t total_q = cu_seqlens[n_seqs];
@@ -508,7 +508,7 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   if (n_seqs > dit::kNoAllocMaxSeqs)
     return fail(ctx, DIT_ATTN_ERR_LIMIT, "dit_attn_varlen_fwd_noalloc takes at most " + std::to_string(dit::kNoAllocMaxSeqs) + " sequences per pack");
   const dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
-                                                        : dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, ctx->n_cus);
+                                                        : dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, head_dim, ctx->n_cus);
   const int32_t bm = dit::attn_fwd_block_m(kernel);
   int64_t n_items = 0;
   for (int32_t i = 0; i < n_seqs; ++i) n_items += static_cast<int64_t>((cu_seqlens[i + 1] - cu_seqlens[i] + bm - 1) / bm) * n_heads;
@@ -532,7 +532,7 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   p.n_heads = n_heads;
   p.c_log2 = std::max(std::fabs(scale) * 1.44269504088896340736f, 1e-30f);
   p.negate = scale < 0.f ? 1 : 0;
-  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel);
+  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel, head_dim);
   e = dit::attn_fwd_launch(p, kernel, head_dim, static_cast<int>(n_items < max_grid ? n_items : max_grid), s);
   if (e != hipSuccess) return fail_hip(ctx, e, "kernel launch");
   ctx->last_kernel = static_cast<int>(kernel);

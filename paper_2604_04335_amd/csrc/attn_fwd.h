@@ -30,7 +30,8 @@ struct AttnParams {
 };
 
 // Two kernels share the tile code.
-//   kIndependent128: 4 wavefronts, 128 query rows per item, two unsynchronised workgroups per compute unit.
+//   kIndependent128: 4 wavefronts, 128 query rows per item, two (head dimension 64: three) unsynchronised workgroups per
+//                    compute unit.
 //   kPingPong256:    8 wavefronts, 256 query rows per item, one workgroup per compute unit whose two wavefront
 //                    groups alternate between the matrix and the vector phase of consecutive tiles.
 enum class AttnKernel : int { kIndependent128 = 0, kPingPong256 = 1 };
@@ -38,11 +39,11 @@ enum class AttnKernel : int { kIndependent128 = 0, kPingPong256 = 1 };
 // Which kernel a pack runs on a device with n_cus compute units (a pure function of the pack).
 // cu_seqlens_k == nullptr: keys share the query boundaries.
 AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_k, int32_t n_seqs, int32_t n_heads,
-                           int n_cus);
+                           int head_dim, int n_cus);
 
 // Query rows per work item and resident workgroups per compute unit of a kernel.
 int attn_fwd_block_m(AttnKernel kernel);
-int attn_fwd_wgs_per_cu(AttnKernel kernel);
+int attn_fwd_wgs_per_cu(AttnKernel kernel, int head_dim);
 
 // Load the code of every attention kernel on the current device and set its LDS limit (a launch would otherwise do both
 // the first time, which allocates; dit_attn_create calls this so that no later launch has to).

@@ -5,12 +5,19 @@
 namespace dit {
 
 // ---------------------------------------------------------------------------------------------
-// Kernel A: 4 wavefronts, 128 query rows per workgroup, two independent workgroups per compute unit.
-// Per tile every wave runs QK, softmax, PV back to back; the two workgroups of a CU overlap each
+// Kernel A: 4 wavefronts, 128 query rows per workgroup, two or three independent workgroups per compute unit.
+// Per tile every wave runs QK, softmax, PV back to back; the workgroups of a CU overlap each
 // other's matrix and vector work without synchronising.  One barrier per tile.
+// At head dimension 64 a tile has as many vector instructions as at 128 and half the MFMAs: the vector ALU bounds it, and
+// a third wavefront per SIMD (144 registers) fills more of its issue slots.  MI355X, two and three workgroups: 4 x 4352
+// rows x 24 heads 526 -> 479 us (ping-pong kernel 520), 20506 x 24 2818 -> 2559 (2601), 8 x 410 x 24 22.6 -> 17.9 (23.4).
+// Four need 128 registers, 14 of them spilled: 488 and 2665.
 // ---------------------------------------------------------------------------------------------
+template <int D>
+constexpr int kWgsPerCu128 = D == 64 ? 3 : 2;
+
 template <class T>
-__global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(2, 2)))
+__global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(kWgsPerCu128<T::D>, kWgsPerCu128<T::D>)))
 attn_fwd_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char* smem = (lds_char*)smem_generic;
@@ -391,35 +398,45 @@ hipError_t attn_fwd_prepare() {
 }
 
 int attn_fwd_block_m(AttnKernel kernel) { return kernel == AttnKernel::kIndependent128 ? 128 : 256; }
-int attn_fwd_wgs_per_cu(AttnKernel kernel) { return kernel == AttnKernel::kIndependent128 ? 2 : 1; }
+int attn_fwd_wgs_per_cu(AttnKernel kernel, int head_dim) {
+  if (kernel != AttnKernel::kIndependent128) return 1;
+  return head_dim == 64 ? kWgsPerCu128<64> : kWgsPerCu128<128>;
+}
 
 AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_k, int32_t n_seqs, int32_t n_heads,
-                           int n_cus) {
-  // Measured on MI355X, head dimension 128 (time of the 128-row kernel over the ping-pong kernel, by 256-row items per
-  // compute unit; 4096-token sequences, 6 to 80 heads): 0.38: 0.99;  0.5: 1.03;  0.62: 1.30;  0.75: 1.23;  0.88: 1.18;
-  // 1.0: 1.16;  1.25: 0.98;  1.5: 1.01;  1.75: 1.11;  2.0: 1.13;  2.5: 1.09;  3.0: 1.22;  3.5: 1.07;  4 and more:
-  // 1.13-1.18; packs of 4352- and 1280-token sequences from 0.94 to 9.6 items per compute unit: 1.07-1.20.  The
-  // ping-pong kernel is ahead whenever its items fill the compute units; the 128-row kernel, whose items are half as
-  // long, when there is under half a 256-row item per compute unit, or (by 2 %) when a second round of 256-row items
-  // would be less than half full.
-  // Items with few key tiles (cross-attention against a few hundred text keys) run better on the 128-row kernel, whose
-  // workgroups have no idle phase at the ends of an item: 64 keys 0.83, 128: 0.89, 226: 0.96, 256: 0.96, 384: 1.02,
-  // 512: 1.04, 768: 1.07, 1024: 1.05, 2048: 1.09.
-  // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still
-  // ramp, whichever kernel runs second looks faster.)
+                           int head_dim, int n_cus) {
+  // Measured on MI355X, us of the 128-row / the ping-pong kernel, rows x heads.
   const int32_t* ck = cu_seqlens_k ? cu_seqlens_k : cu_seqlens;
-  int64_t items256 = 0, tiles = 0;
+  int64_t items128 = 0, items256 = 0, tiles = 0, max_tiles = 0;  // tiles: key tiles of all 256-row items
   for (int32_t i = 0; i < n_seqs; ++i) {
     const int64_t lq = cu_seqlens[i + 1] - cu_seqlens[i], lk = ck[i + 1] - ck[i];
     if (lq == 0 || lk == 0) continue;
-    const int64_t it = (lq + 255) / 256 * n_heads;
+    const int64_t it = (lq + 255) / 256 * n_heads, nt = (lk + 63) / 64;
+    items128 += (lq + 127) / 128 * n_heads;
     items256 += it;
-    tiles += it * ((lk + 63) / 64);
+    tiles += it * nt;
+    max_tiles = nt > max_tiles ? nt : max_tiles;
   }
-  if (items256 * 20 < (int64_t)n_cus * 9) return AttnKernel::kIndependent128;
+  // Compute units to spare for 128-row items: nothing is gained by longer ones.  D 128, under 0.45 256-row items per
+  // compute unit: 1024 x 12 22.3 / 25.0, 1570 x 12 32.3 / 35.5 (at 0.47, 1280 x 24, 29.2 / 30.6).  D 64, as long as every
+  // 128-row item has a compute unit of its own: 1280 x 24 20.1 / 24.1, 410 x 24 8.8 / 11.6;  288 items 17.4 / 15.8.
+  if (head_dim == 64 ? items128 <= n_cus : items256 * 20 < (int64_t)n_cus * 9) return AttnKernel::kIndependent128;
+  // Items with few key tiles (cross-attention against text keys): the 128-row kernel's workgroups have no idle phase at
+  // the ends of an item.  46618 x 24, D 128: 77 keys 142 / 171, 226: 206 / 229, 320: 239 / 259;  D 64: 226 keys 114 / 153.
   if (cu_seqlens_k != nullptr && tiles <= 5 * items256) return AttnKernel::kIndependent128;
-  const int64_t in_second_round = items256 - n_cus;
-  if (in_second_round > 0 && 5 * in_second_round <= 2 * (int64_t)n_cus) return AttnKernel::kIndependent128;
+  // The 256-row items take no longer than the longest of them: the ping-pong kernel's are the quicker ones.  D 128:
+  // 1570 x 24 47.1 / 37.1, 410 and 2458 x 24 81.9 / 70.5;  D 64: 1570 x 24 31.9 / 28.7, 2458 x 24 49.8 / 44.6.
+  if (tiles <= n_cus * max_tiles) return AttnKernel::kPingPong256;
+  // Past one round.  D 64: three workgroups of the 128-row kernel on a compute unit are ahead of the ping-pong kernel
+  // (4 x 4352 x 24 479 / 520, 3 x 1054 x 24 33 / 41, 6000 x 24 253 / 283, 46618 x 24 against 512 keys 185 / 224).
+  if (head_dim == 64) return AttnKernel::kIndependent128;
+  // D 128: the ping-pong kernel (7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
+  // six or seven key tiles (46618 x 24 against 400 keys 307 / 318; 512 keys 339 / 341) and a second round that is at
+  // most 40 % full (2600 x 24 87 / 103, 3200 x 24 145 / 151, 3600 x 24 168 / 169).
+  // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still
+  // ramp, whichever kernel runs second looks faster.)
+  if (cu_seqlens_k != nullptr && tiles <= 7 * items256) return AttnKernel::kIndependent128;
+  if (items256 > n_cus && 5 * (items256 - n_cus) <= 2 * (int64_t)n_cus) return AttnKernel::kIndependent128;
   return AttnKernel::kPingPong256;
 }
 
