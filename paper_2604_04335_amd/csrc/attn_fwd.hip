@@ -428,9 +428,10 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   // 1570 x 24 47.1 / 37.1, 410 and 2458 x 24 81.9 / 70.5;  D 64: 1570 x 24 31.9 / 28.7, 2458 x 24 49.8 / 44.6.
   if (tiles <= n_cus * max_tiles) return AttnKernel::kPingPong256;
   // Past one round.  D 64: three workgroups of the 128-row kernel on a compute unit are ahead of the ping-pong kernel
-  // (4 x 4352 x 24 479 / 520, 3 x 1054 x 24 33 / 41, 6000 x 24 253 / 283, 46618 x 24 against 512 keys 185 / 224).
-  if (head_dim == 64) return AttnKernel::kIndependent128;
-  // D 128: the ping-pong kernel (7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
+  // while items are short, up to 32 key tiles on average (8 x 410 x 24 17.9 / 23.4, 3 x 1054 x 24 33 to 36 / 41, 46618 x 24
+  // against 512 keys 185 / 224); with 47 tiles on average over lengths of 410 to 4250 both are level (363 / 361).
+  if (head_dim == 64 && tiles <= 32 * items256) return AttnKernel::kIndependent128;
+  // Else the ping-pong kernel (D 128: 7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
   // six or seven key tiles (46618 x 24 against 400 keys 307 / 318; 512 keys 339 / 341) and a second round that is at
   // most 40 % full (2600 x 24 87 / 103, 3200 x 24 145 / 151, 3600 x 24 168 / 169).
   // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still

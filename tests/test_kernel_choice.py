@@ -9,7 +9,9 @@ import paper_2604_04335_amd as da
     ([1280], 24, 64, 128),           # 240 items of 128 rows: each has a compute unit of its own
     ([1281], 24, 64, 256),           # 264 of them, 144 items of 256 rows in one round
     ([700] * 4, 12, 64, 256),
-    ([4352] * 4, 24, 64, 128),       # several rounds
+    ([410] * 8, 24, 64, 128),        # several rounds of short items
+    ([2049] * 6, 24, 64, 256),       # 33 key tiles: long items
+    ([2048] * 6, 24, 64, 128),       # 32
     ([4250, 410], 13, 64, 256),      # 247 items, one round
     ([2458, 410], 24, 128, 256),     # 288 items whose second round is made of short ones: no longer than the longest item
     ([2458, 2458], 14, 128, 128),    # 280 equal items: a second round that is nearly empty
