@@ -109,7 +109,7 @@ int dit_attn_varlen_fwd(dit_attn_ctx* ctx,
  * (256 KB + 256 B per GPU, held until the process ends), which also holds the kernels' work counters.
  * Limits: n_seqs <= 64 and at most 16384 work items per pack (an item is 256 query rows of one head, 128 for packs that
  * the 128-row kernel runs; the five benchmark configurations need 32 to 4632); beyond them DIT_ATTN_ERR_LIMIT, `out`
- * untouched.  No split-KV, no plan cache, dit_attn_last_launch_clock is not updated.
+ * untouched.  Unless a kernel is forced, a pack that exceeds the limit only in 128-row items runs the ping-pong kernel.  No split-KV, no plan cache, dit_attn_last_launch_clock is not updated.
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU (two streams, contexts or threads) race;
  * calls on one stream are ordered and safe.  Other return codes as dit_attn_varlen_fwd.
  */

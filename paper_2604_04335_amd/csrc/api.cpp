@@ -507,11 +507,21 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   if (bits & 15u) return fail(ctx, DIT_ATTN_ERR_ALIGN, "q, k, v and out must be 16-byte aligned");
   if (n_seqs > dit::kNoAllocMaxSeqs)
     return fail(ctx, DIT_ATTN_ERR_LIMIT, "dit_attn_varlen_fwd_noalloc takes at most " + std::to_string(dit::kNoAllocMaxSeqs) + " sequences per pack");
-  const dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
-                                                        : dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, head_dim, ctx->n_cus);
+  dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
+                                                  : dit::attn_fwd_select(cu_seqlens, nullptr, n_seqs, n_heads, head_dim, ctx->n_cus);
+  const auto count_items = [&](int64_t block_m) {
+    int64_t n = 0;
+    for (int32_t i = 0; i < n_seqs; ++i) n += (cu_seqlens[i + 1] - cu_seqlens[i] + block_m - 1) / block_m * n_heads;
+    return n;
+  };
+  int64_t n_items = count_items(dit::attn_fwd_block_m(kernel));
+  // The choice goes by time.  A pack whose 128-row items exceed the fixed list may fit it with 256-row items (half as many,
+  // same bits) and is not refused for it.
+  if (n_items > dit::kNoAllocMaxItems && ctx->force_kernel < 0) {
+    kernel = dit::AttnKernel::kPingPong256;
+    n_items = count_items(dit::attn_fwd_block_m(kernel));
+  }
   const int32_t bm = dit::attn_fwd_block_m(kernel);
-  int64_t n_items = 0;
-  for (int32_t i = 0; i < n_seqs; ++i) n_items += static_cast<int64_t>((cu_seqlens[i + 1] - cu_seqlens[i] + bm - 1) / bm) * n_heads;
   if (n_items > dit::kNoAllocMaxItems)
     return fail(ctx, DIT_ATTN_ERR_LIMIT, "dit_attn_varlen_fwd_noalloc takes at most " + std::to_string(dit::kNoAllocMaxItems) +
                                              " work items per pack, this pack has " + std::to_string(n_items));

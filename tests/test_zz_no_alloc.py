@@ -86,3 +86,29 @@ def test_limits_are_refused(ctx):
     w = make_custom([8] * 64, 1, 64, seed=56)
     a, b = _both(ctx, w)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("heads,runs", [(128, da.KERNEL_128), (129, da.KERNEL_PINGPONG), (256, da.KERNEL_PINGPONG), (257, None)])
+def test_items_of_either_height_at_the_limit(ctx, heads, runs):
+    """64 sequences of 129 rows, head dimension 64: the ordinary call runs the 128-row kernel with two items per sequence and
+    head, one with 256 rows.  A pack whose 256-row items fit the list is accepted, with the same bits; beyond it is refused."""
+    print(f"noalloc limit: heads={heads}", flush=True)
+    cu = np.arange(65, dtype=np.int32) * 129
+    gen = torch.Generator(device="cuda").manual_seed(heads)
+    q, k, v = (torch.randn((int(cu[-1]), heads, 64), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(3))
+    stream = torch.cuda.current_stream().cuda_stream
+    out = torch.full(q.shape, SENTINEL, dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    if runs is None:
+        with pytest.raises(da.DitAttnError) as e:
+            da.dit_attn_varlen_fwd_noalloc(ctx, q, k, v, cu, heads, 64, 0.125, out, stream)
+        assert e.value.code == -11 and "work items" in str(e.value)
+        torch.cuda.synchronize()
+        assert bool((out.view(torch.int16) == SENTINEL).all())
+        return
+    ref = torch.empty_like(q)
+    da.dit_attn_varlen_fwd(ctx, q, k, v, cu, heads, 64, 0.125, ref, stream)
+    assert da.dit_attn_last_launch_kernel(ctx) == da.KERNEL_128
+    da.dit_attn_varlen_fwd_noalloc(ctx, q, k, v, cu, heads, 64, 0.125, out, stream)
+    assert da.dit_attn_last_launch_kernel(ctx) == runs
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
