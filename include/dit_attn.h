@@ -195,13 +195,26 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  * Kernel choice of a context.  The library has two kernels for the same
  * operation (which one is fastest depends on the pack, Section 4.3 / Table 3:
  * image steps are short, video steps long):
- *     DIT_ATTN_KERNEL_AUTO   (-1) chosen per pack: the ping-pong kernel when
- *                                 its 256-row items fill the compute units,
- *                                 the 128-row kernel for packs with under half
- *                                 such an item per compute unit, whose second
- *                                 round would be under 40 % full, or
- *                                 (cross-attention) with at most 320 keys per
- *                                 item on average
+ *     DIT_ATTN_KERNEL_AUTO   (-1) chosen per pack from the lengths, n_heads and
+ *                                 head_dim (and the number of compute units):
+ *                                 the 128-row kernel while its items leave
+ *                                 compute units idle (head_dim 128: under 0.45
+ *                                 256-row items per compute unit; head_dim 64:
+ *                                 at most one 128-row item) and for cross-
+ *                                 attention against few keys (320 per item on
+ *                                 average; head_dim 64: 129 to 320); the ping-
+ *                                 pong kernel where the 256-row items take no
+ *                                 longer than the longest of them.  Past that,
+ *                                 head_dim 64: the 128-row kernel up to 100
+ *                                 tiles of 64 keys per item on average, but
+ *                                 not for self-attention whose short items are
+ *                                 two rounds of the ping-pong kernel and more
+ *                                 than one of this, or whose long ones just
+ *                                 fill four of the ping-pong kernel;
+ *                                 else the ping-pong kernel unless its second
+ *                                 round would be at most 40 % full or
+ *                                 (cross-attention) its items have at most
+ *                                 seven such tiles on average
  *     DIT_ATTN_KERNEL_128     (0) 128 query rows per tile
  *     DIT_ATTN_KERNEL_PINGPONG(1) 256 rows per tile, two alternating groups
  * The kernels do the same arithmetic in the same order: their results agree

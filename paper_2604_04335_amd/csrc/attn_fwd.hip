@@ -10,7 +10,7 @@ namespace dit {
 // other's matrix and vector work without synchronising.  One barrier per tile.
 // At head dimension 64 a tile has as many vector instructions as at 128 and half the MFMAs: the vector ALU bounds it, and
 // a third wavefront per SIMD (144 registers) fills more of its issue slots.  MI355X, two and three workgroups: 4 x 4352
-// rows x 24 heads 526 -> 479 us (ping-pong kernel 520), 20506 x 24 2818 -> 2559 (2601), 8 x 410 x 24 22.6 -> 17.9 (23.4).
+// rows x 24 heads 526 -> 479 us, 20506 x 24 2818 -> 2559, 8 x 410 x 24 22.6 -> 17.9.
 // Four need 128 registers, 14 of them spilled: 488 and 2665.
 // ---------------------------------------------------------------------------------------------
 template <int D>
@@ -422,18 +422,40 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   // 128-row item has a compute unit of its own: 1280 x 24 20.1 / 24.1, 410 x 24 8.8 / 11.6;  288 items 17.4 / 15.8.
   if (head_dim == 64 ? items128 <= n_cus : items256 * 20 < (int64_t)n_cus * 9) return AttnKernel::kIndependent128;
   // Items with few key tiles (cross-attention against text keys): the 128-row kernel's workgroups have no idle phase at
-  // the ends of an item.  46618 x 24, D 128: 77 keys 142 / 171, 226: 206 / 229, 320: 239 / 259;  D 64: 226 keys 114 / 153.
-  if (cu_seqlens_k != nullptr && tiles <= 5 * items256) return AttnKernel::kIndependent128;
+  // the ends of an item.  46618 x 24, D 128: 77 keys 142 / 171, 226: 206 / 229, 320: 239 / 259;  D 64: 200 keys 113 / 148.
+  // At D 64 one or two tiles are bound by Q and O, which the larger items move better: 77 keys 108.5 / 103.2, 128 keys
+  // 109.0 / 104.4 (8704 x 24: 25.2 / 24.9 and 25.2 / 25.3).
+  if (cu_seqlens_k != nullptr && tiles <= 5 * items256)
+    return head_dim == 64 && tiles <= 2 * items256 ? AttnKernel::kPingPong256 : AttnKernel::kIndependent128;
   // The 256-row items take no longer than the longest of them: the ping-pong kernel's are the quicker ones.  D 128:
   // 1570 x 24 47.1 / 37.1, 410 and 2458 x 24 81.9 / 70.5;  D 64: 1570 x 24 31.9 / 28.7, 2458 x 24 49.8 / 44.6.
   if (tiles <= n_cus * max_tiles) return AttnKernel::kPingPong256;
-  // Past one round.  D 64: three workgroups of the 128-row kernel on a compute unit are ahead of the ping-pong kernel
-  // while items are short, up to 32 key tiles on average (8 x 410 x 24 17.9 / 23.4, 3 x 1054 x 24 33 to 36 / 41, 46618 x 24
-  // against 512 keys 185 / 224); with 47 tiles on average over lengths of 410 to 4250 both are level (363 / 361).
-  if (head_dim == 64 && tiles <= 32 * items256) return AttnKernel::kIndependent128;
+  // Past one round at D 64 three workgroups of the 128-row kernel share a compute unit and are ahead in general: 512 x 24
+  // heads x 18 sequences 45.9 / 51.5, 1024 x 24 x 9 77.6 / 82.7, 1536 x 24 x 6 105 / 113, 3000 x 24 79 / 98, 3600 x 24
+  // 100 / 119, 4352 x 24 142 / 148, 2049 x 24 x 6 181 / 200, 6000 x 24 257 / 287, 4352 x 24 x 4 483 / 497, 46618 x 24 against
+  // 512 keys 185 / 224.  Ragged batches are between 7 % ahead and level (410 to 4250 rows, 71 items 347 / 346 and 353 / 351;
+  // 421 to 3916 rows 3 % behind).  The exceptions, for self-attention:
+  if (head_dim == 64 && cu_seqlens_k == nullptr) {
+    // Short items that are two rounds for the ping-pong kernel and more than one for the 128-row kernel, whose second round
+    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together, and
+    // the times scatter with the way the items meet): 410 x 24 x 9 27.9 / 24.8, 700 x 24 x 6 39.0 / 32.9, 1054 x 24 x 4
+    // 45 to 57 / 44, 512 x 24 x 9 30.3 / 28.1, 1024 x 24 x 5 46.3 / 45.8, 1300 x 12 x 6 53.3 / 51.0.  Not with the third
+    // round: 1120 x 24 x 5 57.7 / 59.5, 1331 x 12 x 8 63.1 / 66.6, 1024 x 24 x 6 54.6 / 61.4 (three full ones are level or
+    // better: 512 x 24 x 16 41.8 / 42.9, 1024 x 24 x 8 72.0 / 67.6);  not with one round: 300 x 24 x 10 16.6 / 20.2.  Longer
+    // items even it out: 24 tiles (1536 x 24 x 3) 58.5 / 59.7, 28 tiles (1792 x 24 x 3) 72.8 / 72.9.
+    if (tiles <= 24 * items256 && items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus) return AttnKernel::kPingPong256;
+    // Longer items that just fill a fourth round of the ping-pong kernel leave the 128-row kernel a third one half full:
+    // 2458 x 24 x 4 182 / 176, 3750 x 8 x 8 3 % apart, 5120 x 24 x 2 357 / 352, 3000 x 12 x 7 225 / 220.
+    if (tiles > 24 * items256 && 4 * items256 >= 15 * (int64_t)n_cus && items256 <= 4 * (int64_t)n_cus) return AttnKernel::kPingPong256;
+  }
+  // Above 100 key tiles on average either kernel can be ahead: 7500 x 24 372.5 / 374, 16000 x 24 1643 / 1564, 20506 x 24
+  // 2604 / 2639;  the 128-row kernel clearly at 9000 x 24 545 / 573, 12000 x 24 898 / 961 and 8192, 300 and 77 x 12 226 / 258.
+  // With no trend in the size to draw a line by, these stay on the ping-pong kernel.
+  if (head_dim == 64 && tiles <= 100 * items256) return AttnKernel::kIndependent128;
   // Else the ping-pong kernel (D 128: 7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
-  // six or seven key tiles (46618 x 24 against 400 keys 307 / 318; 512 keys 339 / 341) and a second round that is at
-  // most 40 % full (2600 x 24 87 / 103, 3200 x 24 145 / 151, 3600 x 24 168 / 169).
+  // six or seven key tiles (46618 x 24 against 400 keys 301 / 315, 448 keys 302 / 316; 512 keys 332 / 337) and a second round
+  // that is at most 40 % full (2600 x 24 86 / 104, 3200 x 24 145 / 150, 3600 x 24 170 / 171; 41 %, 1500 x 20 x 3, 78.0 / 78.5;
+  // half full, 4000 x 24 193 / 190 and 2000 x 24 x 2 103 / 102; 4352 x 24 245 / 218).
   // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still
   // ramp, whichever kernel runs second looks faster.)
   if (cu_seqlens_k != nullptr && tiles <= 7 * items256) return AttnKernel::kIndependent128;

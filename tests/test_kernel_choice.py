@@ -9,9 +9,22 @@ import paper_2604_04335_amd as da
     ([1280], 24, 64, 128),           # 240 items of 128 rows: each has a compute unit of its own
     ([1281], 24, 64, 256),           # 264 of them, 144 items of 256 rows in one round
     ([700] * 4, 12, 64, 256),
-    ([410] * 8, 24, 64, 128),        # several rounds of short items
-    ([2049] * 6, 24, 64, 256),       # 33 key tiles: long items
-    ([2048] * 6, 24, 64, 128),       # 32
+    ([410] * 8, 24, 64, 128),        # 768 items of 128 rows, three per compute unit
+    ([2049] * 6, 24, 64, 128),       # 33 key tiles
+    ([4352] * 4, 24, 64, 128),
+    ([6400], 24, 64, 128),           # 100 key tiles
+    ([6401], 24, 64, 256),           # 101
+    ([1054] * 4, 24, 64, 256),       # 864 items of 128 rows: a second round of 96 of them
+    ([300] * 10, 24, 64, 128),       # 720: one round
+    ([410] * 8 + [40], 24, 64, 256),       # 792, 408 items of 256 rows
+    ([1024] * 16, 8, 64, 256),       # 1024 items of 128 rows, 512 of 256: two full rounds
+    ([1024] * 16 + [30], 8, 64, 128),      # 520: a third round
+    ([1536] * 3, 24, 64, 256),       # 24 key tiles, 864 items of 128 rows
+    ([1537] * 3, 24, 64, 128),       # 25
+    ([2458] * 4, 24, 64, 256),       # 960 items of 256 rows: a fourth round three quarters full
+    ([2458] * 3 + [2304], 24, 64, 128),    # 936
+    ([4096] * 8, 8, 64, 256),        # 1024: four full rounds
+    ([4096] * 8 + [30], 8, 64, 128),       # 1032
     ([4250, 410], 13, 64, 256),      # 247 items, one round
     ([2458, 410], 24, 128, 256),     # 288 items whose second round is made of short ones: no longer than the longest item
     ([2458, 2458], 14, 128, 128),    # 280 equal items: a second round that is nearly empty
@@ -20,3 +33,27 @@ import paper_2604_04335_amd as da
 def test_kernel_choice(lens, heads, head_dim, block_m):
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     assert da.dit_attn_plan(cu, heads, head_dim)[1] == block_m
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_keys,kernel", [(64, "PINGPONG"), (128, "PINGPONG"), (129, "128"), (320, "128"), (512, "128")])
+def test_cross_choice_at_head_dim_64(n_keys, kernel):
+    """One and two key tiles run the ping-pong kernel, more the 128-row kernel; either gives the bits of the other."""
+    import torch
+    print(f"cross choice: {n_keys} keys", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n_keys)
+    q, k, v = (torch.randn((n, 24, 64), device="cuda", generator=gen).to(torch.bfloat16) for n in (5000, 2 * n_keys, 2 * n_keys))
+    ctx, stream = da.dit_attn_create(0), torch.cuda.current_stream().cuda_stream
+    try:
+        outs = []
+        for forced in (da.KERNEL_AUTO, da.KERNEL_128, da.KERNEL_PINGPONG):
+            da.dit_attn_set_kernel(ctx, forced)
+            outs.append(torch.full_like(q, float("nan")))
+            da.dit_attn_cross_varlen_fwd(ctx, q, k, v, [0, 2600, 5000], [0, n_keys, 2 * n_keys], 24, 64, 0.125, outs[-1], None, stream)
+            if forced == da.KERNEL_AUTO and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+                assert da.dit_attn_last_launch_kernel(ctx) == getattr(da, "KERNEL_" + kernel)
+        torch.cuda.synchronize()
+        assert not bool(outs[0].isnan().any())
+        assert all(torch.equal(outs[0].view(torch.int16), o.view(torch.int16)) for o in outs[1:])
+    finally:
+        da.dit_attn_destroy(ctx)
