@@ -24,10 +24,10 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 }
 
 // U chunks per thread, 256 apart, all their loads issued before the first is used.  SHIFT: log2 of the chunks of a (row,
-// head).  STREAM: the parts are read with streaming loads.
+// head).  STREAM_IN, STREAM_OUT: the parts are read, the output is written past the caches.
 // Four bf16 parts on 49178 rows x 24 heads x 128 (1.5 GB in all), MI355X, us: one chunk per thread and ordinary accesses
-// 281 (5.4 TB/s); streaming loads and stores 261, with two chunks per thread 254, with four 247 (6.2 TB/s).
-template <int P, bool F32, int U, int SHIFT, bool STREAM>
+// 274 (5.5 TB/s); streaming loads and stores 250, with four chunks per thread 245 (6.2 TB/s).
+template <int P, bool F32, int U, int SHIFT, bool STREAM_IN, bool STREAM_OUT>
 __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
   static_assert(!F32 || U == 1, "fp32 parts: one chunk per thread");
   const int64_t e0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;  // 16-byte chunk of the output
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
       l[j][i] = p.lse[i][e >> SHIFT];
       if constexpr (!F32) {
         const u32x4* src = reinterpret_cast<const u32x4*>(p.o[i]) + e;
-        x[j][i] = STREAM ? __builtin_nontemporal_load(src) : *src;
+        x[j][i] = STREAM_IN ? __builtin_nontemporal_load(src) : *src;
       }
     }
   }
@@ -87,29 +87,42 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
     u32x4 y;
 #pragma unroll
     for (int k = 0; k < 4; ++k) y[k] = pack2(acc[2 * k], acc[2 * k + 1]);
-    __builtin_nontemporal_store(y, reinterpret_cast<u32x4*>(p.out) + e);
+    u32x4* dst = reinterpret_cast<u32x4*>(p.out) + e;
+    if constexpr (STREAM_OUT) __builtin_nontemporal_store(y, dst);
+    else *dst = y;
     if (p.lse_out != nullptr && (e & ((1 << SHIFT) - 1)) == 0) p.lse_out[rh] = tot > 0.f ? m_safe + __logf(tot) : -__builtin_inff();
   }
 }
 
-// Parts of this many bytes and more in all are read with streaming loads.  Below, the 256 MB memory-side cache still
-// holds much of what the kernels before wrote: four parts of 295 MB in all 56 us with ordinary loads and 61 us with
-// streaming ones, of 147 MB 27.5 and 30; above, of 590 MB 132 and 120, of 1.2 GB 272 and 247.
-constexpr int64_t kStreamBytes = 400ll << 20;
+// Where parts and output together fit the 256 MB memory-side cache, whoever reads the output next finds it there, and it is
+// written with ordinary stores, one chunk per thread (more workgroups).  Past that it would be evicted anyway and leaves as
+// streaming stores, two chunks per thread from three parts on (two parts of 380 MB and the copy below: 173 us with one
+// chunk per thread, 180 with two, 171 with ordinary stores).
+// Us of a merge on changing buffers and a copy that reads its output, ordinary stores and one chunk / streaming ones and two
+// (in brackets without the copy), by bytes of the parts, MI355X:
+//   two parts   10 MB  7.0 / 7.8 (4.2 / 4.3)    60 MB 26.8 / 29.3 (17.9 / 17.4)   150 MB 69 / 70 (40 / 40)   250 MB 120 / 118 (67 / 65)
+//   four parts  20 MB  9.0 / 10.2 (6.4 / 6.5)   60 MB 21.4 / 23.4 (16.1 / 15.9)   150 MB 47 / 49 (36 / 35)   250 MB  86 / 84 (59 / 56)
+//   eight parts 20 MB  8.3 / 9.8 (6.0 / 7.1)    60 MB 18.4 / 19.3 (15.3 / 14.6)   150 MB 39 / 41 (34 / 32)   270 MB  72 / 71 (59 / 56)
+constexpr int64_t kStreamOutBytes = 256ll << 20;  // of parts and output
+// Parts of this many bytes and more in all are also read with streaming loads, up to four chunks per thread.  The same
+// buffers over and over, ordinary loads / streaming ones: four parts of 147 MB 27.5 / 30, of 295 MB 56 / 61;  of 450 MB
+// 100 / 92, of 600 MB 134 / 123, of 1.2 GB 266 / 245.  With the copy that reads the output, 600 MB 198 / 181, 1.2 GB 388 / 361.
+constexpr int64_t kStreamInBytes = 400ll << 20;
 
-template <int P, bool F32, int U, int SHIFT, bool STREAM>
+template <int P, bool F32, int U, int SHIFT, bool STREAM_IN, bool STREAM_OUT>
 static hipError_t launch(const MergeParams& p, hipStream_t stream) {
   const int64_t blocks = (p.n_chunks + 256 * U - 1) / (256 * U);
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((merge_kernel<P, F32, U, SHIFT, STREAM>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((merge_kernel<P, F32, U, SHIFT, STREAM_IN, STREAM_OUT>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
 template <int P, int SHIFT>
 static hipError_t launch_parts(const MergeParams& p, hipStream_t stream) {
-  if (p.in_f32) return launch<P, true, 1, SHIFT, false>(p, stream);
-  if (P * p.n_chunks * 16 < kStreamBytes) return launch<P, false, 2, SHIFT, false>(p, stream);
-  return launch<P, false, P <= 4 ? 4 : 2, SHIFT, true>(p, stream);  // 64 registers of loads in flight
+  if (p.in_f32) return launch<P, true, 1, SHIFT, false, false>(p, stream);  // split keys: a few rows, read next by the caller
+  if ((P + 1) * p.n_chunks * 16 < kStreamOutBytes) return launch<P, false, 1, SHIFT, false, false>(p, stream);
+  if (P * p.n_chunks * 16 < kStreamInBytes) return launch<P, false, P <= 2 ? 1 : 2, SHIFT, false, true>(p, stream);
+  return launch<P, false, P <= 4 ? 4 : 2, SHIFT, true, true>(p, stream);  // 64 registers of loads in flight
 }
 
 template <int P>

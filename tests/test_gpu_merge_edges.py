@@ -1,4 +1,5 @@
-"""The merge kernel at the edges of its chunks per thread and of the line from which the parts are read with streaming loads."""
+"""The merge kernel at the edges of its chunks per thread and of the lines from which the output is written with streaming
+stores and the parts are read with streaming loads."""
 import pytest
 import torch
 
@@ -43,13 +44,20 @@ def test_chunks_per_thread(n_parts, D, T, H):
     assert float((l.double() - total).abs().max()) <= 1e-5
 
 
-@pytest.mark.parametrize("n_parts", [4, 5])
-def test_either_side_of_the_streaming_line(n_parts):
-    """400 MiB of parts: the last row count below and the first above give the same bits on the rows they share."""
+@pytest.mark.parametrize("n_parts,line", [(2, "stores"), (4, "stores"), (8, "stores"), (4, "loads"), (5, "loads")])
+def test_either_side_of_the_streaming_lines(n_parts, line):
+    """256 MiB of parts and output, 400 MiB of parts: the last row count below and the first above give the same bits on the
+    rows they share (and 24 heads leave a remainder of the chunks per thread on one side of each line)."""
     H, D = 24, 128
-    T = -(-(400 << 20) // (n_parts * H * D * 2))
-    print(f"merge streaming line: parts={n_parts} T={T}", flush=True)
+    T = -(-(256 << 20) // ((n_parts + 1) * H * D * 2)) if line == "stores" else -(-(400 << 20) // (n_parts * H * D * 2))
+    print(f"merge streaming {line}: parts={n_parts} T={T}", flush=True)
     o, lse = _parts(n_parts, T, H, D, n_parts)
     above, l_above = _merge(o, lse)
     below, l_below = _merge([x[:T - 1] for x in o], [x[:T - 1] for x in lse])
     assert torch.equal(above[:T - 1].view(torch.int16), below.view(torch.int16)) and torch.equal(l_above[:T - 1], l_below)
+    rows = torch.arange(T - 700, T, device="cuda")
+    total = torch.logsumexp(torch.stack([x[rows] for x in lse]).double(), 0)
+    ref = sum(torch.exp(x[rows].double() - total)[..., None] * y[rows].double() for x, y in zip(lse, o))
+    # the output's rounding to bf16 and fp32 arithmetic, as above
+    assert bool(((above[rows].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
+    assert float((l_above[rows].double() - total).abs().max()) <= 1e-5
