@@ -94,20 +94,27 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
   }
 }
 
-// Where parts and output together fit the 256 MB memory-side cache, whoever reads the output next finds it there, and it is
-// written with ordinary stores, one chunk per thread (more workgroups).  Past that it would be evicted anyway and leaves as
-// streaming stores, two chunks per thread from three parts on (two parts of 380 MB and the copy below: 173 us with one
-// chunk per thread, 180 with two, 171 with ordinary stores).
-// Us of a merge on changing buffers and a copy that reads its output, ordinary stores and one chunk / streaming ones and two
-// (in brackets without the copy), by bytes of the parts, MI355X:
-//   two parts   10 MB  7.0 / 7.8 (4.2 / 4.3)    60 MB 26.8 / 29.3 (17.9 / 17.4)   150 MB 69 / 70 (40 / 40)   250 MB 120 / 118 (67 / 65)
-//   four parts  20 MB  9.0 / 10.2 (6.4 / 6.5)   60 MB 21.4 / 23.4 (16.1 / 15.9)   150 MB 47 / 49 (36 / 35)   250 MB  86 / 84 (59 / 56)
-//   eight parts 20 MB  8.3 / 9.8 (6.0 / 7.1)    60 MB 18.4 / 19.3 (15.3 / 14.6)   150 MB 39 / 41 (34 / 32)   270 MB  72 / 71 (59 / 56)
-constexpr int64_t kStreamOutBytes = 256ll << 20;  // of parts and output
-// Parts of this many bytes and more in all are also read with streaming loads, up to four chunks per thread.  The same
-// buffers over and over, ordinary loads / streaming ones: four parts of 147 MB 27.5 / 30, of 295 MB 56 / 61;  of 450 MB
-// 100 / 92, of 600 MB 134 / 123, of 1.2 GB 266 / 245.  With the copy that reads the output, 600 MB 198 / 181, 1.2 GB 388 / 361.
-constexpr int64_t kStreamInBytes = 400ll << 20;
+// By the bytes of parts and output: where they fit the 256 MB memory-side cache together, ordinary accesses and one chunk
+// per thread (more workgroups); past that streaming loads, which keep the parts from pushing the output out of that cache
+// before its reader comes, two chunks per thread from three parts on; with kLargeBytes of parts and kStreamOutBytes of output,
+// where the output does not stay there anyway, streaming stores too and up to four chunks per thread.  What counts is the pair of the call and the kernel
+// that reads the output next: a full-speed copy, or 64 workgroups that wait for each line, as a collective does.
+// Us of a merge on changing buffers with the 64-workgroup reader / with a copy / alone, by bytes of the parts, MI355X:
+//                          ordinary              streaming loads       both
+//   four parts   60 MB    34 /  20.9 /  15.8    33 /  19.6 /  14.2    45 /  22.0 /  14.5
+//               220 MB   115 /  75   /  52     102 /  62   /  46     146 /  67   /  46
+//               380 MB   249 / 131   /  90     191 / 116   /  75     250 / 113   /  78
+//               450 MB   310 / 151   / 104     224 / 142   /  88     297 / 133   /  92
+//               1.2 GB   831 / 388   / 273     840 / 382   / 268     815 / 366   / 250
+//   two parts   180 MB   147 /  88   /  48     153 /  79   /  44     213 /  84   /  47
+//               380 MB   452 / 173   / 100     379 / 174   /  95     441 / 174   /  97
+//   eight parts 270 MB    99 /  71   /  59      90 /  62   /  52     115 /  65   /  51
+//               450 MB   186 / 122   /  98     145 / 104   /  87     190 / 109   /  88
+// (Merges of the same buffers over and over want ordinary loads while these fit the cache: four parts of 100 MB 19.5 us and
+// 21.0, of 180 MB 33 and 38.)
+constexpr int64_t kStreamInBytes = 256ll << 20;   // of parts and output
+constexpr int64_t kLargeBytes = 400ll << 20;      // of parts
+constexpr int64_t kStreamOutBytes = 100ll << 20;  // of output
 
 template <int P, bool F32, int U, int SHIFT, bool STREAM_IN, bool STREAM_OUT>
 static hipError_t launch(const MergeParams& p, hipStream_t stream) {
@@ -120,8 +127,8 @@ static hipError_t launch(const MergeParams& p, hipStream_t stream) {
 template <int P, int SHIFT>
 static hipError_t launch_parts(const MergeParams& p, hipStream_t stream) {
   if (p.in_f32) return launch<P, true, 1, SHIFT, false, false>(p, stream);  // split keys: a few rows, read next by the caller
-  if ((P + 1) * p.n_chunks * 16 < kStreamOutBytes) return launch<P, false, 1, SHIFT, false, false>(p, stream);
-  if (P * p.n_chunks * 16 < kStreamInBytes) return launch<P, false, P <= 2 ? 1 : 2, SHIFT, false, true>(p, stream);
+  if ((P + 1) * p.n_chunks * 16 < kStreamInBytes) return launch<P, false, 1, SHIFT, false, false>(p, stream);
+  if (P * p.n_chunks * 16 < kLargeBytes || p.n_chunks * 16 < kStreamOutBytes) return launch<P, false, P <= 2 ? 1 : 2, SHIFT, true, false>(p, stream);
   return launch<P, false, P <= 4 ? 4 : 2, SHIFT, true, true>(p, stream);  // 64 registers of loads in flight
 }
 
