@@ -249,8 +249,9 @@ int64_t dit_attn_plan(const int32_t* cu_seqlens, int32_t n_seqs, int32_t n_heads
 
 namespace {
 
-// Split-KV (opt-in): a pack that leaves compute units idle cuts every sequence's keys into chunks of at least eight key
-// tiles, as many as still run in one round, one workgroup per compute unit, and merges the parts.
+// Split-KV (opt-in): a pack that leaves compute units idle cuts every sequence's keys into chunks, as many as still run in
+// one round, one workgroup per compute unit, and at most one per eight key tiles of the shortest sequence, and merges the
+// parts.  (A sequence's chunks have equal numbers of key tiles but for the last, which takes what is left.)
 // Measured on MI355X, head dimension 128 unless noted, rows x heads: us unsplit / ping-pong kernel (2, 3, 4, 5, 8 chunks) /
 // 128-row kernel (the same):
 //   16384 x 1          284 / 167 131 124 165 134 / 165 161 138 161 147
@@ -262,9 +263,15 @@ namespace {
 //   3 of 2000, 2 heads  39 /  33  30  28  34  40 /  30  32  30  32  37
 //   2500 x 3            47 /  37  30  30  26  28 /  33  27  27  28  28
 //   1570 x 5            31 /  29  26  27  24  27 /  25  22  24  25  28
-// The ping-pong kernel is ahead where a chunk count fills one round of its items; with under 32 key tiles the shorter
-// items of the 128-row kernel are.  The partial results and their merge cost about 9 us, a key tile 1 us per item: a split
-// has to take at least twelve tiles off every item.
+// The ping-pong kernel is ahead where a chunk count fills one round of its items, also with queries of less than 128 rows a
+// sequence (4 of 128 x 24 against 4096 keys each unsplit 72 / 45 / 47, 77 x 24 against 20506 keys 347 / 50 / 55, 3 of 100 x 24
+// against 4352, D 64, 55 / 25 / 26);  with under 32 key tiles the shorter items of the 128-row kernel are.
+// The partial results and their merge cost about 9 us, a key tile 1 us per item of the ping-pong kernel at head dimension 128
+// and less elsewhere.  What a split has to take off every item, unsplit / split in two, at D 128 and D 64:
+//   12 tiles, 128-row kernel    1536 x 10 30.9 / 27.1, 22.4 / 20.2
+//   16 tiles, ping-pong kernel  2048 x 14 41.1 / 42.6, 28.7 / 28.9;  x 16 44.3 / 46.4, 29.4 / 31.0;  x 12 40.2 / 39.8, 28.6 / 27.9
+//   18 tiles                    2304 x 14 48.3 / 49.4, 32.4 / 32.7       20 tiles  2560 x 12 52.3 / 50.8, 35.1 / 34.1
+// With the 128-row kernel forced and more than half of the compute units busy a split gains nothing (4352 x 4 77 / 80).
 void choose_split(const dit_attn_ctx* ctx, const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads,
                   dit::AttnKernel* kernel, int32_t* n_splits) {
   int64_t rows128 = 0, rows256 = 0, min_tiles = INT64_MAX;  // query tiles of either height
@@ -281,7 +288,7 @@ void choose_split(const dit_attn_ctx* ctx, const int32_t* cu_q, const int32_t* c
                                                               : dit::AttnKernel::kPingPong256;
   const int64_t items = (split_kernel == dit::AttnKernel::kIndependent128 ? rows128 : rows256) * n_heads;
   const int64_t n = std::min<int64_t>({ctx->n_cus / items, ctx->max_splits, min_tiles / 8});
-  if (n < 2 || min_tiles - (min_tiles + n - 1) / n < 12) return;
+  if (n < 2 || min_tiles - (min_tiles + n - 1) / n < (split_kernel == dit::AttnKernel::kIndependent128 ? 12 : 17)) return;
   *kernel = split_kernel;
   *n_splits = static_cast<int32_t>(n);
 }

@@ -1,5 +1,6 @@
 """Split keys where the choice of kernel and of the number of chunks changes: 31 and 32 key tiles, a pack whose chunks fill
-the compute units exactly and one that no longer splits, both head dimensions, ragged lengths."""
+the compute units exactly and one that no longer splits, the fewest tiles that a split has to take off an item, a short last
+chunk; both head dimensions, ragged lengths.  The number of chunks and the kernel are checked, and two calls' bits."""
 import pytest
 import torch
 
@@ -22,16 +23,19 @@ def _exact(q, k, v, cu, scale):
     return out, lse
 
 
-@pytest.mark.parametrize("lens,H,D,max_splits,split", [
-    ([4951], 3, 128, 8, True),         # 60 items of 256 rows: four chunks, ping-pong kernel
-    ([1984], 3, 128, 8, True),         # 31 key tiles: three chunks, 128-row kernel
-    ([1985], 3, 64, 8, True),          # 32 key tiles: four chunks, ping-pong kernel, the last of them one key longer
-    ([8192, 8129], 2, 64, 2, True),    # 128 items of 256 rows: two chunks fill 256 compute units
-    ([8193, 8192], 2, 128, 8, False),  # 130 items: no split
-    ([1535], 2, 128, 8, True),         # 24 tiles: three chunks of eight
-    ([1472], 2, 128, 2, False),        # 23 tiles: two chunks take eleven tiles off an item, too few
+@pytest.mark.parametrize("lens,H,D,max_splits,chunks,kernel", [
+    ([4951], 3, 128, 8, 4, da.KERNEL_PINGPONG),         # 60 items of 256 rows: four chunks in one round
+    ([1984], 3, 128, 8, 3, da.KERNEL_128),              # 31 key tiles
+    ([1985], 3, 64, 8, 4, da.KERNEL_PINGPONG),          # 32 key tiles, the last chunk 63 keys shorter than the others
+    ([8192, 8129], 2, 64, 2, 2, da.KERNEL_PINGPONG),    # 128 items of 256 rows: two chunks fill 256 compute units
+    ([8193, 8192], 2, 128, 8, 1, None),                 # 130 items: no split
+    ([1535], 2, 128, 8, 3, da.KERNEL_128),              # 24 tiles: three chunks of eight
+    ([1472], 2, 128, 2, 1, None),                       # 23 tiles: two chunks take eleven tiles off an item, too few
+    ([2112], 14, 64, 8, 1, None),                       # 33 tiles, 126 items of 256 rows: two chunks would take sixteen off
+    ([2176], 14, 64, 8, 2, da.KERNEL_PINGPONG),         # 34 tiles: seventeen
+    ([4160, 4480], 1, 128, 8, 7, da.KERNEL_PINGPONG),   # 35 items; 65 tiles in seven chunks: 10 each, the last 5
 ])
-def test_split_choice(lens, H, D, max_splits, split):
+def test_split_choice(lens, H, D, max_splits, chunks, kernel):
     print(f"split edges: lens={lens} H={H} D={D} max_splits={max_splits}", flush=True)
     cu = [0]
     for n in lens:
@@ -41,14 +45,24 @@ def test_split_choice(lens, H, D, max_splits, split):
     scale, stream = D ** -0.5, torch.cuda.current_stream().cuda_stream
     ctx = da.dit_attn_create(0)
     try:
-        base, out = torch.empty_like(q), torch.full_like(q, float("nan"))
-        lse = torch.full((cu[-1], H), float("nan"), device="cuda")
-        da.dit_attn_varlen_fwd(ctx, q, k, v, cu, H, D, scale, base, stream)
-        da.dit_attn_set_split_kv(ctx, max_splits)
-        da.dit_attn_varlen_fwd_lse(ctx, q, k, v, cu, H, D, scale, out, lse, stream)
+        def run(limit):
+            out, lse = torch.full_like(q, float("nan")), torch.full((cu[-1], H), float("nan"), device="cuda")
+            da.dit_attn_set_split_kv(ctx, limit)
+            da.dit_attn_varlen_fwd_lse(ctx, q, k, v, cu, H, D, scale, out, lse, stream)
+            return out, lse
+
+        out, lse = run(max_splits)
+        used = da.dit_attn_last_launch_kernel(ctx)
+        again, same, base = run(max_splits)[0], run(chunks)[0], run(1)[0]
+        fewer = run(chunks - 1)[0] if chunks > 1 else None
         torch.cuda.synchronize()
+        bits = lambda x: x.view(torch.int16)
+        assert torch.equal(bits(out), bits(again))
         if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-            assert torch.equal(base.view(torch.int16), out.view(torch.int16)) != split
+            # The bits depend on the number of chunks alone: as many as this limit allows, more than one less would.
+            assert torch.equal(bits(out), bits(same)) and torch.equal(bits(out), bits(base)) == (chunks == 1)
+            assert fewer is None or not torch.equal(bits(out), bits(fewer))
+            assert kernel is None or used == kernel
         ref, ref_lse = _exact(q, k, v, cu, scale)
         # the parity bar of the benchmark definition, and the log-sum-exp's ln(1 + 2^-8) of the rounded probabilities
         assert float((out.double() - ref).norm() / ref.norm()) <= 1e-2 and float((out.double() - ref).abs().max()) <= 2e-2
