@@ -61,3 +61,21 @@ def test_either_side_of_the_streaming_lines(n_parts, line):
     # the output's rounding to bf16 and fp32 arithmetic, as above
     assert bool(((above[rows].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
     assert float((l_above[rows].double() - total).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("n_parts,D,T", [(1, 128, 33), (2, 64, 65), (4, 128, 21), (8, 128, 257), (3, 128, 11000), (4, 128, 17500)])
+def test_output_over_a_part(n_parts, D, T):
+    """The output may be the memory of any part: the bits of a merge into memory of its own, in each form of the kernel."""
+    H = 24
+    print(f"merge in place: parts={n_parts} T={T} D={D}", flush=True)
+    o, lse = _parts(n_parts, T, H, D, T)
+    ref, l_ref = _merge(o, lse)
+    ctx = da.dit_attn_create(0)
+    try:
+        for i in sorted({0, n_parts - 1}):
+            mine, l = [x.clone() if j == i else x for j, x in enumerate(o)], torch.full((T, H), float("nan"), device="cuda")
+            da.dit_attn_merge(ctx, mine, lse, T, H, D, mine[i], l, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert torch.equal(mine[i].view(torch.int16), ref.view(torch.int16)) and torch.equal(l, l_ref)
+    finally:
+        da.dit_attn_destroy(ctx)
