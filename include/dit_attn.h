@@ -207,10 +207,10 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  *                                 longer than the longest of them.  Past that,
  *                                 head_dim 64: the 128-row kernel up to 100
  *                                 tiles of 64 keys per item on average, but
- *                                 not for self-attention whose short items are
- *                                 two rounds of the ping-pong kernel and more
- *                                 than one of this, or whose long ones just
- *                                 fill four of the ping-pong kernel;
+ *                                 not for self-attention whose short, well
+ *                                 filled items are two rounds of the ping-pong
+ *                                 kernel and more than one of this, or whose
+ *                                 long ones just fill four of the former;
  *                                 else the ping-pong kernel unless its second
  *                                 round would be at most 40 % full or
  *                                 (cross-attention) its items have at most

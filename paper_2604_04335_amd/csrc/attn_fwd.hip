@@ -407,11 +407,12 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
                            int head_dim, int n_cus) {
   // Measured on MI355X, us of the 128-row / the ping-pong kernel, rows x heads.
   const int32_t* ck = cu_seqlens_k ? cu_seqlens_k : cu_seqlens;
-  int64_t items128 = 0, items256 = 0, tiles = 0, max_tiles = 0;  // tiles: key tiles of all 256-row items
+  int64_t rows = 0, items128 = 0, items256 = 0, tiles = 0, max_tiles = 0;  // tiles: key tiles of all 256-row items
   for (int32_t i = 0; i < n_seqs; ++i) {
     const int64_t lq = cu_seqlens[i + 1] - cu_seqlens[i], lk = ck[i + 1] - ck[i];
     if (lq == 0 || lk == 0) continue;
     const int64_t it = (lq + 255) / 256 * n_heads, nt = (lk + 63) / 64;
+    rows += lq * n_heads;
     items128 += (lq + 127) / 128 * n_heads;
     items256 += it;
     tiles += it * nt;
@@ -437,13 +438,17 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   // 421 to 3916 rows 3 % behind).  The exceptions, for self-attention:
   if (head_dim == 64 && cu_seqlens_k == nullptr) {
     // Short items that are two rounds for the ping-pong kernel and more than one for the 128-row kernel, whose second round
-    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together, and
-    // the times scatter with the way the items meet): 410 x 24 x 9 27.9 / 24.8, 700 x 24 x 6 39.0 / 32.9, 1054 x 24 x 4
-    // 45 to 57 / 44, 512 x 24 x 9 30.3 / 28.1, 1024 x 24 x 5 46.3 / 45.8, 1300 x 12 x 6 53.3 / 51.0.  Not with the third
-    // round: 1120 x 24 x 5 57.7 / 59.5, 1331 x 12 x 8 63.1 / 66.6, 1024 x 24 x 6 54.6 / 61.4 (three full ones are level or
-    // better: 512 x 24 x 16 41.8 / 42.9, 1024 x 24 x 8 72.0 / 67.6);  not with one round: 300 x 24 x 10 16.6 / 20.2.  Longer
-    // items even it out: 24 tiles (1536 x 24 x 3) 58.5 / 59.7, 28 tiles (1792 x 24 x 3) 72.8 / 72.9.
-    if (tiles <= 24 * items256 && items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus) return AttnKernel::kPingPong256;
+    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together; its times
+    // also scatter, 400 x 24 x 9 between 23 and 29 from one run of the program to the next, the ping-pong kernel 24.4 to 25):
+    // 410 x 24 x 9 27.9 / 24.8, 700 x 24 x 6 34.6 to 39 / 32.7, 745 x 24 x 7 40.9 / 36.8, 925 x 12 x 10 45.4 / 40.6, 1054 x 24
+    // x 4 45 to 57 / 44, 512 x 24 x 9 29.0 to 30.3 / 28.5, 1024 x 24 x 5 46.3 / 45.8, 1300 x 12 x 6 53.3 / 51.0.  Not where the
+    // 256-row items hold under 200 rows on average: 520 x 24 x 7 25.8 / 28.7, 588 x 24 x 7 29.3 / 31.0 (610 rows 30.1 / 31.3,
+    // 790 x 24 x 5 36.1 / 36.0);  not with a third round: 1120 x 24 x 5 57.7 / 59.5, 1331 x 12 x 8 63.1 / 66.6, 1024 x 24 x 6
+    // 54.6 / 61.4 (three full ones are level or better: 512 x 24 x 16 41.8 / 42.9, 1024 x 24 x 8 72.0 / 67.6);  not with one
+    // round: 300 x 24 x 10 16.6 / 20.2.  Longer items even it out: 24 tiles 58.5 / 59.7 (1536 x 24 x 3) and 62.7 / 61.7
+    // (1510 x 12 x 7), 28 tiles (1792 x 24 x 3) 72.8 / 72.9.
+    if (tiles <= 24 * items256 && items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus && rows >= 200 * items256)
+      return AttnKernel::kPingPong256;
     // Longer items that just fill a fourth round of the ping-pong kernel leave the 128-row kernel a third one half full:
     // 2458 x 24 x 4 182 / 176, 3750 x 8 x 8 3 % apart, 5120 x 24 x 2 357 / 352, 3000 x 12 x 7 225 / 220.
     if (tiles > 24 * items256 && 4 * items256 >= 15 * (int64_t)n_cus && items256 <= 4 * (int64_t)n_cus) return AttnKernel::kPingPong256;

@@ -16,7 +16,9 @@ import paper_2604_04335_amd as da
     ([6401], 24, 64, 256),           # 101
     ([1054] * 4, 24, 64, 256),       # 864 items of 128 rows: a second round of 96 of them
     ([300] * 10, 24, 64, 128),       # 720: one round
-    ([410] * 8 + [40], 24, 64, 256),       # 792, 408 items of 256 rows
+    ([410] * 8 + [250], 24, 64, 256),      # 816, 408 items of 256 rows
+    ([400] * 9, 24, 64, 256),        # 432 items of 256 rows with 200 rows each on average
+    ([399] * 9, 24, 64, 128),
     ([1024] * 16, 8, 64, 256),       # 1024 items of 128 rows, 512 of 256: two full rounds
     ([1024] * 16 + [30], 8, 64, 128),      # 520: a third round
     ([1536] * 3, 24, 64, 256),       # 24 key tiles, 864 items of 128 rows
