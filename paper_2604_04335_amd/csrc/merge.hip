@@ -9,10 +9,9 @@
 #include <stdint.h>
 
 #include "merge.h"
+#include "store_through.h"
 
 namespace dit {
-
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xFFFF0000u); }
@@ -24,7 +23,7 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 }
 
 // U chunks per thread, 256 apart, all their loads issued before the first is used.  SHIFT: log2 of the chunks of a (row,
-// head).  STREAM_IN, STREAM_OUT: the parts are read, the output is written past the caches.
+// head).  STREAM_IN: the parts are read with streaming loads.  STREAM_OUT: the output is written with streaming stores.
 // Four bf16 parts on 49178 rows x 24 heads x 128 (1.5 GB in all), MI355X, us: one chunk per thread and ordinary accesses
 // 274 (5.5 TB/s); streaming loads and stores 250, with four chunks per thread 245 (6.2 TB/s).
 template <int P, bool F32, int U, int SHIFT, bool STREAM_IN, bool STREAM_OUT>
@@ -89,32 +88,37 @@ __global__ void __launch_bounds__(256) merge_kernel(MergeParams p) {
     for (int k = 0; k < 4; ++k) y[k] = pack2(acc[2 * k], acc[2 * k + 1]);
     u32x4* dst = reinterpret_cast<u32x4*>(p.out) + e;
     if constexpr (STREAM_OUT) __builtin_nontemporal_store(y, dst);
-    else *dst = y;
+    else store_through(dst, y);
     if (p.lse_out != nullptr && (e & ((1 << SHIFT) - 1)) == 0) p.lse_out[rh] = tot > 0.f ? m_safe + __logf(tot) : -__builtin_inff();
   }
 }
 
-// By the bytes of parts and output: where they fit the 256 MB memory-side cache together, ordinary accesses and one chunk
-// per thread (more workgroups); past that streaming loads, which keep the parts from pushing the output out of that cache
-// before its reader comes, two chunks per thread from three parts on; with kLargeBytes of parts and kStreamOutBytes of output,
-// where the output does not stay there anyway, streaming stores too and up to four chunks per thread.  What counts is the pair of the call and the kernel
+// By the bytes of parts and output: ordinary loads and one chunk per thread (more workgroups); from kStreamInBytes on
+// streaming loads, which keep the parts from pushing the output out of the 256 MB memory-side cache before its reader comes,
+// two chunks per thread from three parts on; with kLargeBytes of parts and kStreamOutBytes of output, where the output does
+// not stay there anyway, streaming stores and up to four chunks per thread.  What counts is the pair of the call and the kernel
 // that reads the output next: a full-speed copy, or 64 workgroups that wait for each line, as a collective does.
 // Us of a merge on changing buffers with the 64-workgroup reader / with a copy / alone, by bytes of the parts, MI355X:
-//                          ordinary              streaming loads       both
-//   four parts   60 MB    34 /  20.9 /  15.8    33 /  19.6 /  14.2    45 /  22.0 /  14.5
-//               220 MB   115 /  75   /  52     102 /  62   /  46     146 /  67   /  46
-//               380 MB   249 / 131   /  90     191 / 116   /  75     250 / 113   /  78
-//               450 MB   310 / 151   / 104     224 / 142   /  88     297 / 133   /  92
-//               1.2 GB   831 / 388   / 273     840 / 382   / 268     815 / 366   / 250
-//   two parts   180 MB   147 /  88   /  48     153 /  79   /  44     213 /  84   /  47
-//               380 MB   452 / 173   / 100     379 / 174   /  95     441 / 174   /  97
-//   eight parts 270 MB    99 /  71   /  59      90 /  62   /  52     115 /  65   /  51
-//               450 MB   186 / 122   /  98     145 / 104   /  87     190 / 109   /  88
-// (Merges of the same buffers over and over want ordinary loads while these fit the cache: four parts of 100 MB 19.5 us and
-// 21.0, of 180 MB 33 and 38.)
-constexpr int64_t kStreamInBytes = 256ll << 20;   // of parts and output
+//                          ordinary loads        streaming loads       and streaming stores
+//   four parts   60 MB    33 /  21.0 /  15.8    32 /  19.4 /  13.9    45 /  22.0 /  14.5
+//               100 MB    51 /  32   /  24.2    49 /  29.6 /  21.6    71 /  33.3 /  22.6
+//               220 MB   114 /  74   /  52     100 /  60   /  44     146 /  67   /  46
+//               400 MB   269 / 136   /  93     217 / 128   /  84     265 / 121   /  84
+//               600 MB   417 / 198   / 140     311 / 193   / 129     402 / 182   / 123
+//               1.2 GB   833 / 391   / 278     832 / 377   / 262     809 / 362   / 247
+//   two parts   100 MB    77 /  42   /  28.1    76 /  40   /  24.1
+//               300 MB   360 / 138   /  80     249 / 130   /  73     346 / 133   /  72
+//               600 MB   719 / 269   / 155     721 / 260   / 146     706 / 257   / 142
+//   eight parts  60 MB    25 /  18.5 /  15.4    23 /  17   /  13.7
+//               300 MB   113 /  81   /  65      97 /  69   /  58     127 /  73   /  58
+//               600 MB   256 / 161   / 131     192 / 140   / 110     250 / 143   / 114
+//               780 MB                                    / 163                 / 151   (three sets: their outputs no longer fit)
+// (Parts that all still lie in that cache want ordinary loads: three sets of four parts of 60 MB in turn 12.7 us and 14.1, the
+// same 150 MB over and over 28.3 and 30.7;  all written just before the call, which then counts too, 100 MB 61 and 63, 150 MB
+// 92 and 89.)
+constexpr int64_t kStreamInBytes = 96ll << 20;    // of parts and output
 constexpr int64_t kLargeBytes = 400ll << 20;      // of parts
-constexpr int64_t kStreamOutBytes = 100ll << 20;  // of output
+constexpr int64_t kStreamOutBytes = 80ll << 20;   // of output
 
 template <int P, bool F32, int U, int SHIFT, bool STREAM_IN, bool STREAM_OUT>
 static hipError_t launch(const MergeParams& p, hipStream_t stream) {
@@ -126,7 +130,7 @@ static hipError_t launch(const MergeParams& p, hipStream_t stream) {
 
 template <int P, int SHIFT>
 static hipError_t launch_parts(const MergeParams& p, hipStream_t stream) {
-  if (p.in_f32) return launch<P, true, 1, SHIFT, false, false>(p, stream);  // split keys: a few rows, read next by the caller
+  if (p.in_f32) return launch<P, true, 1, SHIFT, false, false>(p, stream);  // split keys: a few rows
   if ((P + 1) * p.n_chunks * 16 < kStreamInBytes) return launch<P, false, 1, SHIFT, false, false>(p, stream);
   if (P * p.n_chunks * 16 < kLargeBytes || p.n_chunks * 16 < kStreamOutBytes) return launch<P, false, P <= 2 ? 1 : 2, SHIFT, true, false>(p, stream);
   return launch<P, false, P <= 4 ? 4 : 2, SHIFT, true, true>(p, stream);  // 64 registers of loads in flight

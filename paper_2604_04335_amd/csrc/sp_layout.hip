@@ -13,14 +13,13 @@
 #include <stdint.h>
 
 #include "sp_layout.h"
+#include "store_through.h"
 
 namespace dit {
 
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-
 // Index: uint32_t, or uint64_t for a group of 2^32 chunks and more.
 // group_chunks: 16-byte chunks of one (row, head group) = (H/p) * D * 2 / 16;  group_total = n_rows * group_chunks.
-// STREAM_IN, STREAM_OUT: the source is read, the destination is written past the caches.
+// STREAM_IN: the source is read with streaming loads.  STREAM_OUT: the destination is written with streaming stores.
 template <bool PACK, bool STREAM_IN, bool STREAM_OUT, class Index>
 __global__ void __launch_bounds__(256) sp_layout_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, Index group_total,
                                                         uint32_t p, uint32_t group_chunks) {
@@ -32,21 +31,16 @@ __global__ void __launch_bounds__(256) sp_layout_kernel(const u32x4* __restrict_
     const uint64_t grouped = (uint64_t)g * group_total + e;              // [g][row][chunk]
     const uint64_t plain = e + (row * (p - 1) + g) * group_chunks;       // [row][g][chunk]
     const u32x4* from = src + (PACK ? plain : grouped);
-    u32x4* to = dst + (PACK ? grouped : plain);
     const u32x4 x = STREAM_IN ? __builtin_nontemporal_load(from) : *from;
-    if constexpr (STREAM_OUT) __builtin_nontemporal_store(x, to);
-    else *to = x;
+    if constexpr (STREAM_OUT) __builtin_nontemporal_store(x, dst + (PACK ? grouped : plain));
+    else store_through(dst + (PACK ? grouped : plain), x);
   }
 }
 
 template <bool PACK, bool STREAM_IN, bool STREAM_OUT>
 static void launch(const void* src, void* dst, int64_t group_total, uint32_t p, uint32_t group_chunks, hipStream_t stream) {
   int64_t blocks = (group_total + 255) / 256;
-  // Ordinary accesses run better from 4096 workgroups that loop than from one workgroup per 256 chunks ([2000, 40, 128] on
-  // changing buffers 10.0 / 10.5 us, [4000, 40, 128] 16.7 / 17.6); streaming loads the other way round ([12000, 40, 128]
-  // 45 / 43 us, [15500, 40, 128] 60 / 55), and streaming stores do not care.
-  const int64_t cap = STREAM_IN ? 1 << 23 : p < 4096 ? 4096 / p : 1;  // 1 << 23: 2^31 threads
-  if (blocks > cap) blocks = cap;
+  if (blocks > (1 << 23)) blocks = 1 << 23;  // 2^31 threads; the rest by the loop
   const dim3 grid((unsigned)blocks, p), block(256);
   if (group_total <= 0xFFFFFFFFll)
     hipLaunchKernelGGL((sp_layout_kernel<PACK, STREAM_IN, STREAM_OUT, uint32_t>), grid, block, 0, stream, static_cast<const u32x4*>(src),
@@ -56,21 +50,21 @@ static void launch(const void* src, void* dst, int64_t group_total, uint32_t p, 
                        static_cast<u32x4*>(dst), (uint64_t)group_total, p, group_chunks);
 }
 
-// By the size of the tensor: ordinary accesses; from kStreamInBytes on streaming loads, which keep the source from pushing
-// the destination out of the 256 MB memory-side cache before its reader comes; from kStreamOutBytes on, where it does
-// not stay there anyway, streaming stores too.  What counts is the pair of the call and the kernel that reads its destination
-// next: a full-speed copy, or 64 workgroups that wait for each line, as a collective does.
-// Us of a pack of [n, 40, 128] on changing buffers with the 64-workgroup reader / with a copy / alone, MI355X:
-//              ordinary            streaming loads     streaming stores    both
-//     20 MB    32 /  16.2 / 10.0       /  15.7 /  8.8   49 /  18.4 /  9.1        /  18.3 /  8.7
-//     61 MB    85 /  40.8 / 24.1    86 /  41.3 / 23.9  136 /  45.1 / 22.4   136 /  44.9 / 21.6
-//     82 MB   132 /  61.4 / 31.9   119 /  54.2 / 30.3  177 /  58.2 / 29.1   177 /  57.9 / 27.7
-//    123 MB   187 / 104   / 46.7   163 /  86   / 43.1  269 /  92   / 41.8   262 /  84   / 40.2
-//    159 MB   335 / 127   / 60.4   250 / 113   / 54.7  344 / 117   / 53.8   345 / 113   / 51.2
-//    195 MB   442 / 147   / 73.9   363 / 141   / 66.4  424 / 142   / 64.6   427 / 137   / 61.9
-// (Small tensors that are packed again and again in the same two buffers want ordinary loads: 20 MB 6.4 / 7.7, 41 MB
-// 12.5 / 14.6, 82 MB 24.2 / 26.9.)
-constexpr int64_t kStreamInBytes = 75ll << 20;
+// Tensors of kStreamInBytes and more are read with streaming loads, which keep the source from pushing the destination out of
+// the memory-side cache before its reader comes; from kStreamOutBytes on, where it does not stay there anyway, the destination
+// is written with streaming stores instead.  Us of a pack of [n, 40, 128], ordinary / streaming loads with stores written
+// through, streaming loads and stores, MI355X:
+//            three pairs of buffers    many               and a copy of the result   and a reader of 64 workgroups
+//    15 MB    5.5 /  5.7 /  6.4       8.0 /  6.5 /  6.9    13.0 / 12.1 / 14.5          24 /  24 /  37
+//    25 MB    8.2 /  8.7 /  9.8      11.4 / 10.4 / 10.5    18.8 / 17.9 / 21.6          38 /  38 /  59
+//    41 MB   12.4 / 13.4 / 14.5      16.7 / 15.0 / 15.2    27.6 / 26.6 / 31.7          57 /  58 /  92
+//    61 MB   22.2 / 19.0 / 21.0      23.2 / 20.9 / 21.6    39.8 / 37.9 / 44.8          83 /  83 / 135
+//   123 MB   43.7 / 38.8 / 40.2      43.7 / 38.8 / 40.1   103   / 82.5 / 84           206 / 160 / 264
+//   195 MB   70   / 60   / 62        70   / 60   / 62     143   / 133  / 137          433 / 354 / 428
+// A pack and an unpack in turn on three sets of buffers, ordinary / streaming loads: 15 MB 11.4 / 12.7, 20 MB 14.0 / 16.2 (on
+// six sets 15.1 / 13.3 and 19.0 / 16.4);  written through / with streaming stores, streaming loads: 82 MB 57 / 58, 123 MB 82 /
+// 84, 159 MB 108 / 108, 174 MB 118 / 115, 195 MB 134 / 128.  Below 12 MB all are alike (3.6 to 4.4 us a call).
+constexpr int64_t kStreamInBytes = 24ll << 20;
 constexpr int64_t kStreamOutBytes = 160ll << 20;
 
 hipError_t sp_layout_launch(bool pack, const void* src, void* dst, int64_t n_rows, int n_heads, int head_dim, int sp_degree,
