@@ -434,8 +434,9 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   // Past one round at D 64 three workgroups of the 128-row kernel share a compute unit and are ahead in general: 512 x 24
   // heads x 18 sequences 45.9 / 51.5, 1024 x 24 x 9 77.6 / 82.7, 1536 x 24 x 6 105 / 113, 3000 x 24 79 / 98, 3600 x 24
   // 100 / 119, 4352 x 24 142 / 148, 2049 x 24 x 6 181 / 200, 6000 x 24 257 / 287, 4352 x 24 x 4 483 / 497, 46618 x 24 against
-  // 512 keys 185 / 224.  Ragged batches are between 7 % ahead and level (410 to 4250 rows, 71 items 347 / 346 and 353 / 351;
-  // 421 to 3916 rows 3 % behind).  The exceptions, for self-attention:
+  // 512 keys 185 / 224.  Batches of several lengths are between 14 % ahead and 4 % behind: 3167, 537, 876 and 322 rows 89 /
+  // 104, 4 each of 4352, 2458, 1054 and 410 677 / 726, 410 to 4250 rows 355 / 353 to 368, 421 to 3916 rows x 12 170 / 165.
+  // The exceptions, for self-attention:
   if (head_dim == 64 && cu_seqlens_k == nullptr) {
     // Short items that are two rounds for the ping-pong kernel and more than one for the 128-row kernel, whose second round
     // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together; its times
