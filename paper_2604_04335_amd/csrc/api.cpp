@@ -397,9 +397,6 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   }
   const uint32_t n_items = static_cast<uint32_t>(plan->host_items.size());
   if (n_items == 0) return DIT_ATTN_OK;
-  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(plan->kernel, head_dim);
-  const int grid = static_cast<int>(n_items < max_grid ? n_items : max_grid);
-
   const int64_t total_q = cu_seqlens[n_seqs];
   if (n_splits > 1) {
     const size_t need = static_cast<size_t>(n_splits) * static_cast<size_t>(total_q) * static_cast<size_t>(n_heads) *
@@ -455,7 +452,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   p.n_heads = n_heads;
   p.c_log2 = std::max(std::fabs(scale) * 1.44269504088896340736f, 1e-30f);
   p.negate = scale < 0.f ? 1 : 0;
-  e = dit::attn_fwd_launch(p, plan->kernel, head_dim, grid, s);
+  e = dit::attn_fwd_launch(p, plan->kernel, head_dim, ctx->n_cus, plan->host_items.front().kv_len, s);  // most keys first
   if (e != hipSuccess) return fail_hip(ctx, e, "kernel launch");
   ctx->last_kernel = static_cast<int>(plan->kernel);
   if (n_splits > 1) {
@@ -549,8 +546,9 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   p.n_heads = n_heads;
   p.c_log2 = std::max(std::fabs(scale) * 1.44269504088896340736f, 1e-30f);
   p.negate = scale < 0.f ? 1 : 0;
-  const int64_t max_grid = static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel, head_dim);
-  e = dit::attn_fwd_launch(p, kernel, head_dim, static_cast<int>(n_items < max_grid ? n_items : max_grid), s);
+  int32_t max_keys = 0;
+  for (int32_t i = 0; i < n_seqs; ++i) max_keys = std::max(max_keys, cu_seqlens[i + 1] - cu_seqlens[i]);
+  e = dit::attn_fwd_launch(p, kernel, head_dim, ctx->n_cus, max_keys, s);
   if (e != hipSuccess) return fail_hip(ctx, e, "kernel launch");
   ctx->last_kernel = static_cast<int>(kernel);
   return DIT_ATTN_OK;

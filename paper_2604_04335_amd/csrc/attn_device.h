@@ -68,12 +68,13 @@ constexpr int kPrefetch = 4;
 
 // BN keys form one tile: the unit of the softmax (one reference-value decision per row and tile) and of the loads.
 // A K or V buffer holds SUBS consecutive tiles; the ping-pong kernel works through SUBS = 2 tiles per phase.
-template <int D_, int NWAVES_, int BN_, int SUBS_ = 1>
+template <int D_, int NWAVES_, int BN_, int SUBS_ = 1, int NBUF_ = 2>
 struct Tile {
   static constexpr int D = D_;
   static constexpr int NWAVES = NWAVES_;
   static constexpr int BN = BN_;
   static constexpr int SUBS = SUBS_;
+  static constexpr int NBUF = NBUF_;               // K and V buffers each
   static constexpr int NT = NWAVES * 64;           // threads
   static constexpr int BM = NWAVES * 32;           // query rows per workgroup
   static constexpr int ROW_B = D * 2;              // bytes of one K/V row of one head
@@ -90,9 +91,9 @@ struct Tile {
   // LDS: [K buffer 0][K buffer 1][V buffer 0][V buffer 1][two item slots], a buffer = SUBS tiles
   static constexpr int BUF_B = SUBS * TILE_B;
   static constexpr int K_OFF = 0;
-  static constexpr int V_OFF = 2 * BUF_B;
-  static constexpr int ITEM_OFF = 4 * BUF_B;
-  static constexpr int LDS_BYTES = 4 * BUF_B + 16;
+  static constexpr int V_OFF = NBUF * BUF_B;
+  static constexpr int ITEM_OFF = 2 * NBUF * BUF_B;
+  static constexpr int LDS_BYTES = 2 * NBUF * BUF_B + 16;
   static_assert(GROUP % 16 == 0 && BN % GROUP == 0, "load rounds must keep row%16 fixed per lane");
   static_assert(D == 64 || D == 128, "head dimension");
 
@@ -115,6 +116,17 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 __device__ __forceinline__ float add_prob_pair(float acc, uint32_t packed) {
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, packed), ones, acc, false);
+}
+// The row sum of one tile's rounded probabilities: one chain of v_dot2c, issued back to back behind an MFMA stream of the
+// same wavefront.
+template <class T>
+__device__ __forceinline__ float row_sum(const uint32_t (&pb)[T::NKB][8]) {
+  float lsum = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < T::NKB; ++kb)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lsum = add_prob_pair(lsum, pb[kb][i]);
+  return lsum;
 }
 
 // Per-lane constants of a kernel instance.
@@ -172,6 +184,15 @@ __device__ __forceinline__ void lds_dma_16(const char* sbase, uint32_t voff, uin
                : "memory");
 }
 
+// The same to LDS byte base + OFF, OFF known at compile time.
+template <int OFF>
+__device__ __forceinline__ void lds_dma_16_at(const char* sbase, uint32_t voff, uint32_t base) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(base), "v"(voff), "s"(sbase), "n"(OFF)
+               : "memory", "scc");
+}
+
 // The last tile of a sequence may be partial.  If the sequence has at least BN keys the tile is loaded as the LAST BN
 // keys of the sequence (rows [kv_len - BN, kv_len): an ordinary full-tile load, whose first rows repeat keys of the
 // tile before and are masked out of the softmax); only a sequence shorter than one tile needs per-lane clamping.
@@ -197,15 +218,6 @@ __device__ __forceinline__ int tile_first_key(int ti, int kv_len) {
 
 // Rows past the end of a sequence shorter than a tile re-read its last key (their scores are masked, and a finite V
 // row times a zero probability adds nothing).
-// Load instruction i (0 .. LPT-1) of this wave's share of a tile that is known to be whole (every tile of a sequence
-// of at least BN keys): rows i*GROUP + lrow, no branch.
-template <class T>
-__device__ __forceinline__ void tile_load_part_whole(const char* base, int64_t row_stride_b, int key0, uint32_t voff,
-                                                     lds_char* smem, int dst_off, int wave, int i) {
-  const char* sbase = base + (int64_t)(key0 + i * T::GROUP) * row_stride_b;  // scalar
-  lds_dma_16(sbase, voff, (uint32_t)(uintptr_t)smem + (uint32_t)dst_off + (uint32_t)wave * 1024u + (uint32_t)(i * T::NWAVES * 1024));
-}
-
 // This wave's whole share of the tile that starts at key0 = tile_first_key(..): LPT instructions, one test.
 template <class T>
 __device__ __forceinline__ void tile_load_one(const char* base, int64_t row_stride_b, int key0, int kv_len, int lrow,
@@ -426,33 +438,9 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // How far (in the base-2 exponent) a tile's row maximum may exceed the row's reference value before the reference moves.
 constexpr float kRescaleLog2 = 8.0f;
 
-// Online softmax of one tile: scores s -> bf16 probabilities pb (B-operand order), reference max / sum, lazy rescale.
-// Element i of block kb is key 32*kb + 8*(i/4) + 4*hh + (i%4) of the tile, for query lane%32.
-// PHASED (the ping-pong kernel) leaves two things to the matrix phase that follows: the row sums (row_sum_burst below;
-// a v_dot2c shares the matrix pipe and, issued here, would queue behind the MFMA stream that the other wavefront of the
-// SIMD runs meanwhile: about 60 cycles each instead of 5), and, with DEFER (the second tile of a pair), the rescale of
-// O^T and l, which in a tile-by-tile pass comes after the first tile's PV MFMAs and row sum.  The function returns the
-// mask of rows whose reference moved (zero: nothing to do) and, with DEFER, their factors in alpha_out (1 for rows
-// that stayed, and for every row when the mask is zero); m_ref is updated here in every variant.
-template <class T, bool TAIL, bool PHASED = false, bool DEFER = false>
-__device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, TailRows rows, float c,
-                                                 uint32_t (&pb)[T::NKB][8], f32x16 (&o)[T::NDB], float& m_ref,
-                                                 float& l_run, float* alpha_out = nullptr) {
-  static_assert(PHASED || !DEFER, "a deferred rescale needs the phased row sums");
-  // Tail mask.  Element i of block kb is key 32 kb + 8 (i / 4) + (i % 4) + 4 hh: the key is dead (not a new key of this
-  // tile) unless lo <= key < hi, tested as one unsigned compare of a compile-time constant against two per-lane
-  // values.  (With the per-lane part folded into the key instead, the compiler keeps all 32 key indices of a lane
-  // in registers across the whole kernel and turns the masking into branches around the exponentials.)
-  const int tail_lo = rows.lo - 4 * hh;
-  const unsigned tail_n = (unsigned)(rows.hi - rows.lo);
-  auto dead = [&](int kb, int i) { return (unsigned)(32 * kb + 8 * (i >> 2) + (i & 3) - tail_lo) >= tail_n; };
-  if (TAIL) {
-#pragma unroll
-    for (int kb = 0; kb < T::NKB; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[kb][i] = dead(kb, i) ? -__builtin_inff() : s[kb][i];
-  }
-
+// Maximum over a tile's scores for this lane's query row (both halves of the wavefront).
+template <class T>
+__device__ __forceinline__ float tile_max(const f32x16 (&s)[T::NKB]) {
   // v_max3_f32 written out, one asm statement per block of 16 scores: through fmaxf the compiler first "quiets"
   // every operand it cannot prove canonical with a v_max_f32 x, x, x (MFMA results, asm results), six more
   // instructions per tile; and it pads every asm statement with an s_nop.
@@ -474,7 +462,35 @@ __device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, Ta
           DIT_S(kb, 8), DIT_S(kb, 9), DIT_S(kb, 10), DIT_S(kb, 11), DIT_S(kb, 12), DIT_S(kb, 13), DIT_S(kb, 14),
           DIT_S(kb, 15));
 #undef DIT_S
-  mx = max_with_other_half(mx);
+  return max_with_other_half(mx);
+}
+
+// Online softmax of one tile: scores s -> bf16 probabilities pb (B-operand order), reference max, lazy rescale.
+// Element i of block kb is key 32*kb + 8*(i/4) + 4*hh + (i%4) of the tile, for query lane%32.
+// The row sums are the caller's (row_sum, behind an MFMA stream of its own).  DEFER (the second tile of a pair in the
+// ping-pong kernel) also leaves the rescale of O^T and l to the matrix phase that follows, which in a tile-by-tile pass
+// comes after the first tile's PV MFMAs and row sum.  The function returns the mask of rows whose reference moved (zero:
+// nothing to do) and, with DEFER, their factors in alpha_out (1 for rows that stayed, and for every row when the mask is
+// zero); m_ref is updated here in every variant.
+template <class T, bool TAIL, bool DEFER = false>
+__device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, TailRows rows, float c,
+                                                 uint32_t (&pb)[T::NKB][8], f32x16 (&o)[T::NDB], float& m_ref,
+                                                 float& l_run, float* alpha_out = nullptr) {
+  // Tail mask.  Element i of block kb is key 32 kb + 8 (i / 4) + (i % 4) + 4 hh: the key is dead (not a new key of this
+  // tile) unless lo <= key < hi, tested as one unsigned compare of a compile-time constant against two per-lane
+  // values.  (With the per-lane part folded into the key instead, the compiler keeps all 32 key indices of a lane
+  // in registers across the whole kernel and turns the masking into branches around the exponentials.)
+  const int tail_lo = rows.lo - 4 * hh;
+  const unsigned tail_n = (unsigned)(rows.hi - rows.lo);
+  auto dead = [&](int kb, int i) { return (unsigned)(32 * kb + 8 * (i >> 2) + (i & 3) - tail_lo) >= tail_n; };
+  if (TAIL) {
+#pragma unroll
+    for (int kb = 0; kb < T::NKB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] = dead(kb, i) ? -__builtin_inff() : s[kb][i];
+  }
+
+  const float mx = tile_max<T>(s);
 
   // The reference value m_ref of a row follows its running maximum lazily: it moves (and O^T and l are rescaled) only
   // when the tile's maximum exceeds it by more than kRescaleLog2 in the exponent, so probabilities lie in
@@ -503,7 +519,6 @@ __device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, Ta
 
   // Eight scores at a time, with a scheduling fence after each group: the probabilities are packed to bf16 and
   // their fp32 values die before the next group starts, which keeps the register peak of this phase low.
-  float lsum = 0.f;
 #pragma unroll
   for (int kb = 0; kb < T::NKB; ++kb) {
 #pragma unroll
@@ -513,36 +528,144 @@ __device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, Ta
         float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], c, -mc));
         float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i + 1], c, -mc));
         pb[kb][i >> 1] = pack_bf16x2(p0, p1);  // a dead key: score -inf, c > 0 (AttnParams::c_log2), probability 0
-        if constexpr (!PHASED) lsum = add_prob_pair(lsum, pb[kb][i >> 1]);
       }
       SCHED_FENCE();
     }
   }
-  if constexpr (!PHASED) {
-    l_run += lsum;
-  } else {
-    // Everything above is finished here: the compiler otherwise sinks the exponentials of a tile towards their first
-    // use, which lies behind a barrier, inside the matrix phase.
+  // Everything above is finished here: the compiler otherwise sinks the exponentials of a tile towards their first
+  // use, which (in the ping-pong kernel) lies behind a barrier, inside the matrix phase.
 #pragma unroll
-    for (int kb = 0; kb < T::NKB; ++kb)
-      asm volatile("" : "+v"(pb[kb][0]), "+v"(pb[kb][1]), "+v"(pb[kb][2]), "+v"(pb[kb][3]), "+v"(pb[kb][4]), "+v"(pb[kb][5]),
-                        "+v"(pb[kb][6]), "+v"(pb[kb][7]));
-    asm volatile("" : "+v"(l_run), "+v"(m_ref));
-  }
+  for (int kb = 0; kb < T::NKB; ++kb)
+    asm volatile("" : "+v"(pb[kb][0]), "+v"(pb[kb][1]), "+v"(pb[kb][2]), "+v"(pb[kb][3]), "+v"(pb[kb][4]), "+v"(pb[kb][5]),
+                      "+v"(pb[kb][6]), "+v"(pb[kb][7]));
+  asm volatile("" : "+v"(l_run), "+v"(m_ref));
   return grown;
 }
 
-// The row sum of one tile's rounded probabilities, in the order tile_softmax adds them: one chain of v_dot2c, issued
-// back to back.  The ping-pong kernel calls it at the end of a wavefront's matrix phase, when the matrix pipe of the
-// SIMD is this wavefront's own.
+// The reference value of the rows whose tile maximum mx exceeds it by more than kRescaleLog2 moves to mx; O^T and l of
+// such a row are rescaled.
 template <class T>
-__device__ __forceinline__ float row_sum_burst(const uint32_t (&pb)[T::NKB][8]) {
-  float lsum = 0.f;
+__device__ __forceinline__ void raise_reference(float mx, float c, f32x16 (&o)[T::NDB], float& m_ref, float& l_run) {
+  const bool grow = (mx - m_ref) * c > kRescaleLog2;
+  if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+    const float m_new = grow ? mx : m_ref;
+    const float alpha = __builtin_amdgcn_exp2f((m_ref - m_new) * c);
+    m_ref = m_new;
+    l_run *= alpha;
 #pragma unroll
-  for (int kb = 0; kb < T::NKB; ++kb)
+    for (int db = 0; db < T::NDB; ++db)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lsum = add_prob_pair(lsum, pb[kb][i]);
-  return lsum;
+      for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+  }
+}
+
+// One step of the 128-row kernel: the exponentials of tile t beside the MFMAs of S^T(t+1) = K(t+1) Q^T and of
+// O^T += V(t)^T P(t)^T in one instruction stream, then the maximum of S^T(t+1) beside the last of them.
+//
+// Behind every MFMA of the stream (a slot) stand the operand read of a later MFMA and a share of the vector work that fits
+// beside it.  The order of the MFMAs of one accumulator is that of a tile-by-tile pass, so the results are the same bits.
+// Slots: QK(t+1) first (its scores are complete early enough for their maximum), beside the probabilities of key block 0;
+// then PV(t) block by block.  With Q K and P V the other way round nothing would be left beside the last MFMAs.
+template <class T>
+struct StepSlots {
+  static constexpr int N = T::NQK + T::NPV;  // MFMA slots: QK(t+1), then PV(t)
+  static constexpr int UNITS = T::NKB * 8;   // pairs of scores of a lane
+  // Slot behind whose MFMA pair k of the tile's scores becomes a pair of probabilities.
+  static constexpr int slot(int k) {
+    if (T::D == 64) return k < 8 ? k : k < 14 ? 8 + (k - 8) * 2 / 3 : k - 2;
+    return k < 8 ? 2 * k : 16 + (k - 8) * 3 / 2;
+  }
+  static constexpr int first_unit(int j) {
+    int k = 0;
+    while (k < UNITS && slot(k) < j) ++k;
+    return k;
+  }
+  static constexpr int max_slot0 = N - 4;  // four slots take the maximum, eight scores each
+};
+
+template <class T, int KOFF, int VOFF, int PD, class Issue>
+__device__ __forceinline__ void tile_step(const int (&va_)[T::NDB], const int (&ka_)[T::NKS], uint32_t (&pb)[T::NKB][8],
+                                          const bf16x8 (&qf)[T::NKS], f32x16 (&o)[T::NDB], f32x16 (&sc)[T::NKB],
+                                          f32x16 (&sn)[T::NKB], float c, float mc, float& mx, Issue&& issue) {
+  using S = StepSlots<T>;
+  constexpr int NQ = T::NQK, N = S::N;
+  static_assert(T::NKB == 2, "two key blocks per tile");
+  bf16x8 frag[PD];
+  auto load_step = [&](auto jc) {
+    constexpr int J = decltype(jc)::value;
+    if constexpr (J >= NQ) {
+      constexpr int j = J - NQ, kb = j / (2 * T::NDB), u = (j / T::NDB) % 2, db = j % T::NDB;
+      lds_char* p0 = (lds_char*)(uintptr_t)(uint32_t)(va_[db] + VOFF + (32 * kb + 16 * u) * T::ROW_B);
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p0));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p0 + 8 * T::ROW_B));
+      frag[J % PD] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      constexpr int ks = J / T::NKB, kb = J % T::NKB;
+      frag[J % PD] = *(lds_bf16x8*)(uintptr_t)(uint32_t)(ka_[ks] + KOFF + kb * 32 * T::ROW_B);
+    }
+  };
+  auto mfma = [&](auto jc) {
+    constexpr int J = decltype(jc)::value;
+    if constexpr (J >= NQ) {
+      constexpr int j = J - NQ, kb = j / (2 * T::NDB), u = (j / T::NDB) % 2, db = j % T::NDB;
+      static_assert(S::slot(8 * kb + 4 * u + 4 < S::UNITS ? 8 * kb + 4 * u + 4 : S::UNITS - 1) < J, "probabilities before their MFMA");
+      u32x4 pw = {pb[kb][4 * u], pb[kb][4 * u + 1], pb[kb][4 * u + 2], pb[kb][4 * u + 3]};
+      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[J % PD], __builtin_bit_cast(bf16x8, pw), o[db], 0, 0, 0);
+    } else {
+      constexpr int ks = J / T::NKB, kb = J % T::NKB;
+      if constexpr (ks == 0) {
+        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        sn[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[J % PD], qf[ks], zero, 0, 0, 0);
+      } else {
+        sn[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[J % PD], qf[ks], sn[kb], 0, 0, 0);
+      }
+    }
+  };
+  // Pair k of the scores; its conversion follows behind the exponentials of pair k + 1 (a conversion may not follow the
+  // exponential it reads at once).
+  float e0 = 0.f, e1 = 0.f;
+  auto unit = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    float f0 = 0.f, f1 = 0.f;
+    if constexpr (k < S::UNITS) {
+      constexpr int kb = k / 8, i = 2 * (k % 8);
+      f0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][i], c, -mc));
+      f1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kb][i + 1], c, -mc));
+    }
+    if constexpr (k > 0) {
+      SCHED_FENCE();
+      pb[(k - 1) / 8][(k - 1) % 8] = pack_bf16x2(e0, e1);
+    }
+    e0 = f0;
+    e1 = f1;
+  };
+  SCHED_FENCE();
+  static_for<0, PD>([&](auto jc) { load_step(jc); });
+  SCHED_FENCE();
+  static_for<0, N>([&](auto jc) {
+    constexpr int J = decltype(jc)::value;
+    mfma(jc);
+    if constexpr (J + PD < N) load_step(IC<J + PD>{});
+    SCHED_FENCE();
+    static_for<S::first_unit(J), S::first_unit(J + 1)>(unit);
+    if constexpr (S::slot(S::UNITS - 1) == J) unit(IC<S::UNITS>{});
+    issue(jc);
+    if constexpr (J >= S::max_slot0) {
+      constexpr int m = J - S::max_slot0, kb = m / 2, i = 8 * (m % 2);
+      if constexpr (m == 0)
+        asm("v_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5\n\tv_max3_f32 %0, %0, %6, %7\n\tv_max_f32 %0, %0, %8"
+            : "=&v"(mx)
+            : "v"(sn[0][0]), "v"(sn[0][1]), "v"(sn[0][2]), "v"(sn[0][3]), "v"(sn[0][4]), "v"(sn[0][5]), "v"(sn[0][6]), "v"(sn[0][7]));
+      else
+        asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\tv_max3_f32 %0, %0, %5, %6\n\tv_max3_f32 %0, %0, %7, %8"
+            : "+v"(mx)
+            : "v"(sn[kb][i]), "v"(sn[kb][i + 1]), "v"(sn[kb][i + 2]), "v"(sn[kb][i + 3]), "v"(sn[kb][i + 4]), "v"(sn[kb][i + 5]),
+              "v"(sn[kb][i + 6]), "v"(sn[kb][i + 7]));
+    }
+    SCHED_FENCE();
+  });
+  mx = max_with_other_half(mx);
+  SCHED_FENCE();
 }
 
 // All LDS accesses of this wave are complete, then workgroup barrier.  The "memory" clobber keeps the

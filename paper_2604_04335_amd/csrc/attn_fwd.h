@@ -49,8 +49,9 @@ int attn_fwd_wgs_per_cu(AttnKernel kernel, int head_dim);
 // the first time, which allocates; dit_attn_create calls this so that no later launch has to).
 hipError_t attn_fwd_prepare();
 
-// Enqueue the forward kernel with `grid` persistent workgroups.
-hipError_t attn_fwd_launch(const AttnParams& p, AttnKernel kernel, int head_dim, int grid, hipStream_t stream);
+// Enqueue the forward kernel with persistent workgroups (at most attn_fwd_wgs_per_cu of them per compute unit) on a device
+// with n_cus compute units.  max_keys: the most keys of any item.
+hipError_t attn_fwd_launch(const AttnParams& p, AttnKernel kernel, int head_dim, int n_cus, int32_t max_keys, hipStream_t stream);
 
 }  // namespace dit
 

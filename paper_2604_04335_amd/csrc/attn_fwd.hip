@@ -5,30 +5,62 @@
 namespace dit {
 
 // ---------------------------------------------------------------------------------------------
-// Kernel A: 4 wavefronts, 128 query rows per workgroup, two or three independent workgroups per compute unit.
-// Per tile every wave runs QK, softmax, PV back to back; the workgroups of a CU overlap each
-// other's matrix and vector work without synchronising.  One barrier per tile.
-// At head dimension 64 a tile has as many vector instructions as at 128 and half the MFMAs: the vector ALU bounds it, and
-// a third wavefront per SIMD (144 registers) fills more of its issue slots.  MI355X, two and three workgroups: 4 x 4352
-// rows x 24 heads 526 -> 479 us, 20506 x 24 2818 -> 2559, 8 x 410 x 24 22.6 -> 17.9.
-// Four need 128 registers, 14 of them spilled: 488 and 2665.
+// Kernel A: 4 wavefronts, 128 query rows per workgroup.  The workgroups of a compute unit do not synchronise.
+//
+// A wavefront works one tile ahead (tile_step): the scores of tile t+1 are contracted while tile t goes through its
+// exponentials and into O^T, so that its matrix and vector instructions overlap inside one instruction stream.  With the
+// three back to back the two pipes of a SIMD took turns unless another wavefront happened to be at the right place: a
+// wavefront alone on its SIMD used each of them a third of the time.  Alone it is bound by its own instruction issue (about
+// five cycles each, 195 instructions a tile at head dimension 64), which is why the main loop has neither address
+// arithmetic (slots of the K / V rings are immediate offsets, the loads run on pointers) nor tests.  MI355X, us, back to
+// back / as it is: 1024 rows x 8 heads, D 64 15.7 / 12.5;  16384 x 1, D 64 199 / 136;  410 x 24, D 64 8.7 / 7.8;  image
+// batch, D 64 (410 to 4250 rows x 24) 352 / 330;  9000 x 24, D 64 545 / 493;  1024 x 8, D 128 22.1 / 19.1;  4951 x 3,
+// D 128 88.5 / 69.6.
+//
+// Two K and V ring slots let several workgroups share a compute unit: three at head dimension 64, two at 128 (a third
+// wavefront per SIMD at 64, in 165 registers, fills more of the issue slots: image batch 344 with two, 332 with three).
+// Four slots are for workgroups that have a compute unit to themselves (head dimension 128): a barrier every second tile,
+// and the loads spread over a tile instead of a burst in which the four wavefronts wait for one another on the way to
+// memory.  16384 x 1 216 / 187, 4951 x 3 69.6 / 62.0, 1024 x 8 19.1 / 18.4; at 64, with half the loads, 137 / 136.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 constexpr int kWgsPerCu128 = D == 64 ? 3 : 2;
 
 template <class T>
-__global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(kWgsPerCu128<T::D>, kWgsPerCu128<T::D>)))
+constexpr int kWavesPerSimd = T::NBUF > 2 ? 2 : kWgsPerCu128<T::D>;
+
+template <class T>
+__global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(kWavesPerSimd<T>, kWavesPerSimd<T>)))
 attn_fwd_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char* smem = (lds_char*)smem_generic;
   lds_slot* s_item = reinterpret_cast<lds_slot*>(smem + T::ITEM_OFF);
 
+  constexpr int NB = T::NBUF;
   const LaunchClock clock0 = launch_clock_begin();
   const int tid = threadIdx.x;
   const int64_t row_stride_b = (int64_t)p.n_heads * T::D * 2;
   const float c = p.c_log2;
-  Lane<T> L;
-  L.init(tid, row_stride_b);
+  // Per-lane constants are recomputed where an item starts or ends; kept live through the tile loop they are spilled.
+  auto fresh_lane = [&]() {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    Lane<T> l;
+    l.init(t, row_stride_b);
+    return l;
+  };
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t kvoff[T::LPT], vvoff[T::LPT];  // lane offsets of the load instructions of a whole tile
+  {
+    const Lane<T> L0 = fresh_lane();
+#pragma unroll
+    for (int i = 0; i < T::LPT; ++i) {
+      kvoff[i] = L0.kvoff + (uint32_t)(i * T::GROUP) * (uint32_t)row_stride_b;
+      vvoff[i] = L0.vvoff + (uint32_t)(i * T::GROUP) * (uint32_t)row_stride_b;
+    }
+  }
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)smem + (uint32_t)wave * 1024u;
+  const int64_t tile_stride_b = (int64_t)T::BN * row_stride_b;
 
   // The index of the next item is requested towards the end of an item, into the slot of the other parity; a barrier
   // between that write and the end of the item makes it visible to every wave before it is read.
@@ -38,17 +70,30 @@ attn_fwd_kernel(AttnParams p) {
 
   while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
-    const ItemCtx<T> X = begin_item<T>(p, L, item_idx, row_stride_b);
+    const ItemCtx<T> X = begin_item<T>(p, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;
 
-    auto load_tile = [&](int ti) {  // K(ti), V(ti) -> buffers of parity ti&1
-      tile_load_one<T>(X.kbase, row_stride_b, tile_first_key<T>(ti, kv_len), kv_len, L.lrow, L.kcol, L.kvoff, smem, T::K_OFF + (ti & 1) * T::TILE_B, L.wave);
-      tile_load_one<T>(X.vbase, row_stride_b, tile_first_key<T>(ti, kv_len), kv_len, L.lrow, L.vcol, L.vvoff, smem, T::V_OFF + (ti & 1) * T::TILE_B, L.wave);
+    // Tile ti -> its ring slot.  Only for sequences of two tiles or more, whose tiles are all loaded whole.
+    auto load_k = [&](int ti) {
+      const char* base = X.kbase + (int64_t)tile_first_key<T>(ti, kv_len) * row_stride_b;
+      const uint32_t dst = lds_wave + T::K_OFF + (uint32_t)(ti & (NB - 1)) * T::TILE_B;
+#pragma unroll
+      for (int i = 0; i < T::LPT; ++i) lds_dma_16(base, kvoff[i], dst + i * T::NWAVES * 1024);
     };
-    load_tile(0);
-
+    auto load_v = [&](int ti) {
+      const char* base = X.vbase + (int64_t)tile_first_key<T>(ti, kv_len) * row_stride_b;
+      const uint32_t dst = lds_wave + T::V_OFF + (uint32_t)(ti & (NB - 1)) * T::TILE_B;
+#pragma unroll
+      for (int i = 0; i < T::LPT; ++i) lds_dma_16(base, vvoff[i], dst + i * T::NWAVES * 1024);
+    };
     bf16x8 qf[T::NKS];
-    load_q<T>(p, L, X.it, row_stride_b, X.head_off, X.qrow, qf);
+    {
+      const Lane<T> L = fresh_lane();
+      tile_load_one<T>(X.kbase, row_stride_b, 0, kv_len, L.lrow, L.kcol, kvoff[0], smem, T::K_OFF, wave);
+      load_q<T>(p, L, X.it, row_stride_b, X.head_off, X.qrow, qf);
+      tile_load_one<T>(X.vbase, row_stride_b, 0, kv_len, L.lrow, L.vcol, vvoff[0], smem, T::V_OFF, wave);
+    }
+    if (nt > 1) load_k(1);
 
     f32x16 o[T::NDB];
 #pragma unroll
@@ -56,49 +101,122 @@ attn_fwd_kernel(AttnParams p) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
     float m_ref = -1.0e30f;  // finite: (m_ref - m) * c stays finite
-    float l_run = 0.f;
-    f32x16 s[T::NKB];
+    float l_run = 0.f, mx = 0.f;
+    f32x16 sa[T::NKB], sb[T::NKB];
     uint32_t pb[T::NKB][8];
-    int ka[T::NKS], va[T::NDB];  // operand addresses in the buffers of the current tile's parity
-    L.operand_addrs((uint32_t)(uintptr_t)smem, (uint32_t)(uintptr_t)smem, ka, va);
+    int ka[T::NKS], va[T::NDB];
+    fresh_lane().operand_addrs((uint32_t)(uintptr_t)smem, (uint32_t)(uintptr_t)smem, ka, va);
 
     if (nt == 1 && tid == 0 && !one_round) s_item[par] = take_item(p);  // visible after the barrier below
-    for (int t = 0; t + 1 < nt; ++t) {
-      // Tile t has landed (this wave's loads), and after the barrier everyone's; everyone is also done
-      // reading the other buffers (tile t-1), so they can be refilled with tile t+1 while tile t is used.
+    wait_loads();
+    if (NB > 2 && nt > 2) load_k(2);
+    if (NB > 2 && nt > 1) load_v(1);
+    wg_barrier();
+    mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, sa);
+    if (nt > 1) mx = tile_max<T>(sa);
+    // Step t: S(t) is in sc; leaves S(t+1) in sn.  Every PER_BAR steps there is a barrier, behind which K(t+1) and V(t) (with
+    // two steps to a barrier also K(t+2) and V(t+1)) have landed for everyone and nobody reads the tiles before them any
+    // more: their slots take the tiles behind them.  A step of the main loop (MAIN) loads tiles that are not a sequence's
+    // last, from running pointers.
+    constexpr int PER_BAR = NB / 2;
+    const char* kp = X.kbase + (PER_BAR + 1) * tile_stride_b;
+    const char* vp = X.vbase + PER_BAR * tile_stride_b;
+    constexpr bool SPREAD = NB > 2;
+    constexpr int NSLOT = T::NQK + T::NPV, NLOAD = 2 * PER_BAR * T::LPT, EVERY = NSLOT / NLOAD;
+    auto step = [&](auto uc, auto mainc, f32x16(&sc)[T::NKB], f32x16(&sn)[T::NKB], int t) {
+      constexpr int U = decltype(uc)::value;  // t % UNROLL in the main loop, t % 2 behind it
+      constexpr bool MAIN = decltype(mainc)::value;
+      constexpr bool BAR = U % PER_BAR == 0;
+      if constexpr (BAR) {
+        wait_loads();
+        wg_barrier();
+      }
+      const bool ask = !MAIN && t + 2 == nt && tid == 0 && !one_round;
+      uint32_t next_item = 0;
+      auto load_i = [&](auto jc) {
+        constexpr int j = decltype(jc)::value, i = j % T::LPT, n = j / (2 * T::LPT);
+        if constexpr (j / T::LPT % 2 == 0)
+          lds_dma_16_at<T::K_OFF + (U + PER_BAR + 1 + n) % NB * T::TILE_B + i * T::NWAVES * 1024>(kp + n * tile_stride_b, kvoff[i], lds_wave);
+        else
+          lds_dma_16_at<T::V_OFF + (U + PER_BAR + n) % NB * T::TILE_B + i * T::NWAVES * 1024>(vp + n * tile_stride_b, vvoff[i], lds_wave);
+      };
+      if constexpr (!MAIN) {
+        if (ask) next_item = take_item(p);
+        if constexpr (BAR) {
+#pragma unroll
+          for (int n = 0; n < PER_BAR; ++n) {
+            if (t + PER_BAR + 1 + n < nt) load_k(t + PER_BAR + 1 + n);
+            if (t + PER_BAR + n < nt) load_v(t + PER_BAR + n);
+          }
+        }
+      } else if constexpr (BAR && !SPREAD) {
+        static_for<0, NLOAD>(load_i);
+      }
+      raise_reference<T>(mx, c, o, m_ref, l_run);
+      const float mc = m_ref * c;
+      tile_step<T, MAIN ? (U + 1) % NB * T::TILE_B : 0, MAIN ? U % NB * T::TILE_B : 0, kPrefetch>(
+          va, ka, pb, qf, o, sc, sn, c, mc, mx, [&](auto jc) {
+            constexpr int J = decltype(jc)::value;
+            if constexpr (MAIN && BAR && SPREAD && J % EVERY == EVERY / 2 && J / EVERY < NLOAD) load_i(IC<J / EVERY>{});
+          });
+      if constexpr (MAIN) {
+        if constexpr (BAR) {
+          kp += PER_BAR * tile_stride_b;
+          vp += PER_BAR * tile_stride_b;
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < T::NKS; ++ks) ka[ks] ^= (((t + 1) ^ (t + 2)) & (NB - 1)) * T::TILE_B;
+#pragma unroll
+        for (int db = 0; db < T::NDB; ++db) va[db] ^= ((t ^ (t + 1)) & (NB - 1)) * T::TILE_B;
+      }
+      l_run += row_sum<T>(pb);
+      asm volatile("" : "+v"(l_run));
+      if (ask) s_item[par] = next_item;
+    };
+    static_assert(NB == 2 || NB == 4, "slots by exclusive or; the parity of the scores follows t");
+    constexpr int UNROLL = NB;
+    int t = 0;
+    for (; t + UNROLL + PER_BAR + 1 < nt; t += UNROLL)
+      static_for<0, UNROLL / 2>([&](auto ic) {
+        constexpr int I = 2 * decltype(ic)::value;
+        step(IC<I>{}, IC<1>{}, sa, sb, t + I);
+        step(IC<I + 1>{}, IC<1>{}, sb, sa, t + I + 1);
+      });
+    // The last steps: t is a multiple of NB here; the addresses follow the slots.
+#pragma unroll
+    for (int ks = 0; ks < T::NKS; ++ks) ka[ks] ^= T::TILE_B;
+    for (; t + 2 < nt; t += 2) {
+      step(IC<0>{}, IC<0>{}, sa, sb, t);
+      step(IC<1>{}, IC<0>{}, sb, sa, t + 1);
+    }
+    if (t + 1 < nt) {
+      step(IC<0>{}, IC<0>{}, sa, sb, t);
+#pragma unroll
+      for (int kb = 0; kb < T::NKB; ++kb) sa[kb] = sb[kb];
+    }
+    if (nt > 1) {
       wait_loads();
       wg_barrier();
-      // The next index is requested here and put into its slot at the end of the tile (visible after the barrier of
-      // the last tile): the request takes about a microsecond to come back, which thread 0's wavefront spends on
-      // the tile instead of waiting.
-      const bool ask = t + 2 == nt && tid == 0 && !one_round;
-      uint32_t next_item = 0;
-      if (ask) next_item = take_item(p);
-      load_tile(t + 1);
-      mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, s);
-      tile_softmax<T, false>(s, L.hh, TailRows{0, T::BN}, c, pb, o, m_ref, l_run);
-      mfma_stream<T, true, 0, 0, kPrefetch>(smem, va, ka, pb, qf, o, s);
-      if (ask) s_item[par] = next_item;
-#pragma unroll
-      for (int ks = 0; ks < T::NKS; ++ks) ka[ks] ^= T::TILE_B;
-#pragma unroll
-      for (int db = 0; db < T::NDB; ++db) va[db] ^= T::TILE_B;
     }
-    // The last tile (masked), outside the loop: one copy of each softmax variant, no test per tile.
-    wait_loads();
-    wg_barrier();
-    mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, s);
-    tile_softmax<T, true>(s, L.hh, tail_rows<T>(kv_len), c, pb, o, m_ref, l_run);
-    mfma_stream<T, true, 0, 0, kPrefetch>(smem, va, ka, pb, qf, o, s);
+    const Lane<T> L = fresh_lane();
+    tile_softmax<T, true>(sa, L.hh, tail_rows<T>(kv_len), c, pb, o, m_ref, l_run);
+    mfma_stream<T, true, 0, 0, kPrefetch>(smem, va, ka, pb, qf, o, sa);
+    l_run += row_sum<T>(pb);
 
-    // The rows are staged in the buffers of the parity that the last tile does not use: every wavefront is done with
-    // tile nt - 2 (the barrier of the last tile), nothing is being loaded there, and the next item's loads come after
-    // the barrier below.  Wavefronts 0, 1 take the K buffer of that parity, wavefronts 2, 3 the V buffer.
-    const uint32_t stage = (uint32_t)(uintptr_t)smem + (L.wave < 2 ? T::K_OFF : T::V_OFF) + (nt & 1) * T::TILE_B +
-                           (uint32_t)(L.wave & 1) * (32 * T::ROW_B);
-    store_out<T>(p, L, X.it, row_stride_b, X.head_off, X.qrow, X.row_valid, o, l_run, m_ref, stage);
+    // The rows are staged where nobody reads or loads any more behind the barrier of the last tile: in the K ring, and for
+    // what it does not hold in the V slots of other tiles than the last.
+    int qrow = L.wave * 32 + L.l32;
+    const bool row_valid = qrow < X.it.q_rows;
+    if (!row_valid) qrow = X.it.q_rows - 1;
+    constexpr int PER = T::TILE_B / (32 * T::ROW_B);  // wavefronts per slot
+    const int sl = wave / PER;
+    const uint32_t stage = (uint32_t)(uintptr_t)smem + (uint32_t)(wave % PER) * (32 * T::ROW_B) +
+                           (nt > 1 ? T::K_OFF + sl * T::TILE_B : sl + 1 < NB ? T::K_OFF + (sl + 1) * T::TILE_B : T::V_OFF + T::TILE_B);
+    static_assert(T::NWAVES / PER <= NB, "staging area");
+    store_out<T>(p, L, X.it, row_stride_b, X.head_off, qrow, row_valid, o, l_run, m_ref, stage);
     if (one_round) break;
-    wg_barrier();  // the next item's first loads overwrite the buffers of parity 0
+    wg_barrier();  // the next item's first loads overwrite ring slot 0
     item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
   }
   launch_clock_end(p, clock0);
@@ -307,15 +425,15 @@ attn_fwd_pp_kernel(AttnParams p) {
       if (ask) next_item = take_item(p);
       if (group == 1) load_v_pair_all(t + 1);            // read from phase 2t+4 on
       if (group == 0) load_k_pair_all(t + 1);  // read from the next phase on
-      tile_softmax<T, false, true>(s[0], 0, TailRows{0, T::BN}, c, pb[0], o, m_ref, l_run);  // no mask: hh unused
-      grown = tile_softmax<T, false, true, true>(s[1], 0, TailRows{0, T::BN}, c, pb[1], o, m_ref, l_run, &alpha1);
+      tile_softmax<T, false>(s[0], 0, TailRows{0, T::BN}, c, pb[0], o, m_ref, l_run);  // no mask: hh unused
+      grown = tile_softmax<T, false, true>(s[1], 0, TailRows{0, T::BN}, c, pb[1], o, m_ref, l_run, &alpha1);
       if (group == 0) wait_loads();
       if (ask) s_item[par] = next_item;
       wg_barrier();
       // ---- matrix phase: PV(Pt), QK(Pt+1)
       __builtin_amdgcn_s_setprio(1);
       pp_stream<T, 2, 2, kPrefetch>(va, ka, pb, qf, o, s, grown, alpha1);
-      l_run = (l_run + row_sum_burst<T>(pb[0])) * alpha1 + row_sum_burst<T>(pb[1]);
+      l_run = (l_run + row_sum<T>(pb[0])) * alpha1 + row_sum<T>(pb[1]);
       asm volatile("" : "+v"(l_run));  // the sums are taken here, not behind the barrier
       __builtin_amdgcn_s_setprio(0);
 #pragma unroll
@@ -327,20 +445,20 @@ attn_fwd_pp_kernel(AttnParams p) {
     }
     // ---- last pair: two tiles or one, the last of them masked; PV only
     if ((nt & 1) == 0) {
-      tile_softmax<T, false, true>(s[0], 0, TailRows{0, T::BN}, c, pb[0], o, m_ref, l_run);
-      grown = tile_softmax<T, true, true, true>(s[1], fresh_lane().hh, tail_rows<T>(kv_len), c, pb[1], o, m_ref, l_run, &alpha1);
+      tile_softmax<T, false>(s[0], 0, TailRows{0, T::BN}, c, pb[0], o, m_ref, l_run);
+      grown = tile_softmax<T, true, true>(s[1], fresh_lane().hh, tail_rows<T>(kv_len), c, pb[1], o, m_ref, l_run, &alpha1);
       wg_barrier();
       __builtin_amdgcn_s_setprio(1);
       pp_stream<T, 2, 0, kPrefetch>(va, ka, pb, qf, o, s, grown, alpha1);
-      l_run = (l_run + row_sum_burst<T>(pb[0])) * alpha1 + row_sum_burst<T>(pb[1]);
+      l_run = (l_run + row_sum<T>(pb[0])) * alpha1 + row_sum<T>(pb[1]);
       asm volatile("" : "+v"(l_run));  // the sums are taken here, not behind the barrier
       __builtin_amdgcn_s_setprio(0);
     } else {
-      tile_softmax<T, true, true>(s[0], fresh_lane().hh, tail_rows<T>(kv_len), c, pb[0], o, m_ref, l_run);
+      tile_softmax<T, true>(s[0], fresh_lane().hh, tail_rows<T>(kv_len), c, pb[0], o, m_ref, l_run);
       wg_barrier();
       __builtin_amdgcn_s_setprio(1);
       pp_stream<T, 1, 0, kPrefetch>(va, ka, pb, qf, o, s, 0, 1.f);
-      l_run += row_sum_burst<T>(pb[0]);
+      l_run += row_sum<T>(pb[0]);
       asm volatile("" : "+v"(l_run));
       __builtin_amdgcn_s_setprio(0);
     }
@@ -393,6 +511,7 @@ hipError_t attn_fwd_prepare() {
   hipError_t e = prepare_t<Tile<128, 8, 64, 2>, attn_fwd_pp_kernel<Tile<128, 8, 64, 2>>>();
   if (e == hipSuccess) e = prepare_t<Tile<64, 8, 64, 2>, attn_fwd_pp_kernel<Tile<64, 8, 64, 2>>>();
   if (e == hipSuccess) e = prepare_t<Tile<128, 4, 64>, attn_fwd_kernel<Tile<128, 4, 64>>>();
+  if (e == hipSuccess) e = prepare_t<Tile<128, 4, 64, 1, 4>, attn_fwd_kernel<Tile<128, 4, 64, 1, 4>>>();
   if (e == hipSuccess) e = prepare_t<Tile<64, 4, 64>, attn_fwd_kernel<Tile<64, 4, 64>>>();
   return e;
 }
@@ -469,11 +588,19 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   return AttnKernel::kPingPong256;
 }
 
-hipError_t attn_fwd_launch(const AttnParams& p, AttnKernel kernel, int head_dim, int grid, hipStream_t stream) {
+hipError_t attn_fwd_launch(const AttnParams& p, AttnKernel kernel, int head_dim, int n_cus, int32_t max_keys, hipStream_t stream) {
+  const int64_t max_grid = (int64_t)n_cus * attn_fwd_wgs_per_cu(kernel, head_dim);
+  const int grid = (int)(p.n_items < max_grid ? p.n_items : max_grid);
   if (kernel != AttnKernel::kIndependent128) {
     if (head_dim == 128) return launch_t<Tile<128, 8, 64, 2>, attn_fwd_pp_kernel<Tile<128, 8, 64, 2>>>(p, grid, stream);
     if (head_dim == 64) return launch_t<Tile<64, 8, 64, 2>, attn_fwd_pp_kernel<Tile<64, 8, 64, 2>>>(p, grid, stream);
   } else {
+    // Four ring slots where no compute unit has two items (see the kernel).  Two / four slots, rows x heads: on a chip that is
+    // at most half full from 13 key tiles on (700 x 8 14.3 / 14.4, 832 x 8 16.0 / 15.4, 1024 x 8 19.2 / 18.3, 2048 x 3 31.6 /
+    // 28.3, 4096 x 4 59 / 53), on a fuller one from 28 on (1024 x 24 21.8 / 22.5, 1500 x 20 31.3 / 32.2, 2048 x 16 39.7 / 39.4,
+    // 4096 x 8 70.3 / 66.7, 8192 x 4 133 / 125): below, the longer start of an item weighs more.
+    if (head_dim == 128 && p.n_items <= (uint32_t)n_cus && max_keys > 64 * (2 * p.n_items <= (uint32_t)n_cus ? 12 : 27))
+      return launch_t<Tile<128, 4, 64, 1, 4>, attn_fwd_kernel<Tile<128, 4, 64, 1, 4>>>(p, grid, stream);
     if (head_dim == 128) return launch_t<Tile<128, 4, 64>, attn_fwd_kernel<Tile<128, 4, 64>>>(p, grid, stream);
     if (head_dim == 64) return launch_t<Tile<64, 4, 64>, attn_fwd_kernel<Tile<64, 4, 64>>>(p, grid, stream);
   }
