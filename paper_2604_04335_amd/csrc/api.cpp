@@ -437,7 +437,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
     }
   }
 
-  dit::AttnParams p;
+  dit::AttnParams p{};
   p.part_out = part_out;
   p.part_lse = part_lse;
   p.part_rows = total_q;
@@ -452,7 +452,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   p.n_heads = n_heads;
   p.c_log2 = std::max(std::fabs(scale) * 1.44269504088896340736f, 1e-30f);
   p.negate = scale < 0.f ? 1 : 0;
-  e = dit::attn_fwd_launch(p, plan->kernel, head_dim, ctx->n_cus, plan->host_items.front().kv_len, s);  // most keys first
+  e = dit::attn_fwd_launch(p, nullptr, plan->kernel, head_dim, ctx->n_cus, plan->host_items.front().kv_len, s);  // most keys first
   if (e != hipSuccess) return fail_hip(ctx, e, "kernel launch");
   ctx->last_kernel = static_cast<int>(plan->kernel);
   if (n_splits > 1) {
@@ -534,21 +534,25 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   if (e != hipSuccess) return fail_hip(ctx, e, "hipSetDevice");
   hipStream_t s = static_cast<hipStream_t>(stream);
   dit::AttnParams p{};
-  const dit::WorkItem* items = nullptr;
-  e = dit::noalloc_plan_launch(ctx->device, cu_seqlens, n_seqs, n_heads, bm, static_cast<uint32_t>(n_items), s, &items, &p.sync);
-  if (e != hipSuccess) return fail_hip(ctx, e, "work-list kernel launch");
+  dit::PackList list;
+  if (n_items <= static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel, head_dim) &&
+      dit::pack_list_build(cu_seqlens, cu_seqlens, n_seqs, n_heads, bm, list)) {
+    p.sync = dit::noalloc_sync(ctx->device);
+  } else {
+    e = dit::noalloc_plan_launch(ctx->device, cu_seqlens, n_seqs, n_heads, bm, static_cast<uint32_t>(n_items), s, &p.items, &p.sync);
+    if (e != hipSuccess) return fail_hip(ctx, e, "work-list kernel launch");
+  }
   p.q = q;
   p.k = k;
   p.v = v;
   p.out = out;
-  p.items = items;
   p.n_items = static_cast<uint32_t>(n_items);
   p.n_heads = n_heads;
   p.c_log2 = std::max(std::fabs(scale) * 1.44269504088896340736f, 1e-30f);
   p.negate = scale < 0.f ? 1 : 0;
   int32_t max_keys = 0;
   for (int32_t i = 0; i < n_seqs; ++i) max_keys = std::max(max_keys, cu_seqlens[i + 1] - cu_seqlens[i]);
-  e = dit::attn_fwd_launch(p, kernel, head_dim, ctx->n_cus, max_keys, s);
+  e = dit::attn_fwd_launch(p, p.items ? nullptr : &list, kernel, head_dim, ctx->n_cus, max_keys, s);
   if (e != hipSuccess) return fail_hip(ctx, e, "kernel launch");
   ctx->last_kernel = static_cast<int>(kernel);
   return DIT_ATTN_OK;

@@ -29,9 +29,10 @@ constexpr int kWgsPerCu128 = D == 64 ? 3 : 2;
 template <class T>
 constexpr int kWavesPerSimd = T::NBUF > 2 ? 2 : kWgsPerCu128<T::D>;
 
-template <class T>
+template <class T, class P>
 __global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(kWavesPerSimd<T>, kWavesPerSimd<T>)))
-attn_fwd_kernel(AttnParams p) {
+attn_fwd_kernel(P p) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs the kernel's name only, and fails on the second instance of a body
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char* smem = (lds_char*)smem_generic;
   lds_slot* s_item = reinterpret_cast<lds_slot*>(smem + T::ITEM_OFF);
@@ -70,7 +71,7 @@ attn_fwd_kernel(AttnParams p) {
 
   while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
-    const ItemCtx<T> X = begin_item<T>(p, fresh_lane(), item_idx, row_stride_b);
+    const ItemCtx<T> X = begin_item<T, P>(p, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;
 
     // Tile ti -> its ring slot.  Only for sequences of two tiles or more, whose tiles are all loaded whole.
@@ -220,6 +221,7 @@ attn_fwd_kernel(AttnParams p) {
     item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
   }
   launch_clock_end(p, clock0);
+#endif
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -246,9 +248,10 @@ attn_fwd_kernel(AttnParams p) {
 // longest phase by ~500 cycles.  A sequence with an odd number of tiles ends in a pair of one tile; the QK MFMAs of the
 // missing tile run on whatever its buffer half holds and their scores are never read.
 // ---------------------------------------------------------------------------------------------
-template <class T>
+template <class T, class P>
 __global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(2, 2)))
-attn_fwd_pp_kernel(AttnParams p) {
+attn_fwd_pp_kernel(P p) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs the kernel's name only, and fails on the second instance of a body
   static_assert(T::NWAVES == 8 && T::SUBS == 2, "two groups of four wavefronts, two tiles per phase");
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char* smem = (lds_char*)smem_generic;
@@ -287,7 +290,7 @@ attn_fwd_pp_kernel(AttnParams p) {
 
   while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
-    const ItemCtx<T> X = begin_item<T>(p, fresh_lane(), item_idx, row_stride_b);
+    const ItemCtx<T> X = begin_item<T, P>(p, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;  // nt: 64-key tiles
     const int npairs = (nt + 1) >> 1;
 
@@ -482,10 +485,11 @@ attn_fwd_pp_kernel(AttnParams p) {
     item_idx = __builtin_amdgcn_readfirstlane(s_item[par]);
   }
   launch_clock_end(p, clock0);
+#endif
 }
 
 // The LDS limit of a kernel is set once per device (its first use there also loads the kernel's code).
-template <class T, void (*KERNEL)(AttnParams)>
+template <class T, class P, void (*KERNEL)(P)>
 static hipError_t prepare_t() {
   static bool attr_set[16] = {};
   int dev = 0;
@@ -499,21 +503,32 @@ static hipError_t prepare_t() {
   return hipSuccess;
 }
 
-template <class T, void (*KERNEL)(AttnParams)>
-static hipError_t launch_t(const AttnParams& p, int grid, hipStream_t stream) {
-  const hipError_t e = prepare_t<T, KERNEL>();
+template <class T, class P, void (*KERNEL)(P)>
+static hipError_t launch_t(const P& p, int grid, hipStream_t stream) {
+  const hipError_t e = prepare_t<T, P, KERNEL>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(T::NT), T::LDS_BYTES, stream, p);
   return hipGetLastError();
 }
 
-hipError_t attn_fwd_prepare() {
-  hipError_t e = prepare_t<Tile<128, 8, 64, 2>, attn_fwd_pp_kernel<Tile<128, 8, 64, 2>>>();
-  if (e == hipSuccess) e = prepare_t<Tile<64, 8, 64, 2>, attn_fwd_pp_kernel<Tile<64, 8, 64, 2>>>();
-  if (e == hipSuccess) e = prepare_t<Tile<128, 4, 64>, attn_fwd_kernel<Tile<128, 4, 64>>>();
-  if (e == hipSuccess) e = prepare_t<Tile<128, 4, 64, 1, 4>, attn_fwd_kernel<Tile<128, 4, 64, 1, 4>>>();
-  if (e == hipSuccess) e = prepare_t<Tile<64, 4, 64>, attn_fwd_kernel<Tile<64, 4, 64>>>();
+using TilePP128 = Tile<128, 8, 64, 2>;
+using TilePP64 = Tile<64, 8, 64, 2>;
+using Tile128 = Tile<128, 4, 64>;
+using Tile128Deep = Tile<128, 4, 64, 1, 4>;
+using Tile64 = Tile<64, 4, 64>;
+
+template <class P>
+static hipError_t prepare_all() {
+  hipError_t e = prepare_t<TilePP128, P, attn_fwd_pp_kernel<TilePP128, P>>();
+  if (e == hipSuccess) e = prepare_t<TilePP64, P, attn_fwd_pp_kernel<TilePP64, P>>();
+  if (e == hipSuccess) e = prepare_t<Tile128, P, attn_fwd_kernel<Tile128, P>>();
+  if (e == hipSuccess) e = prepare_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>();
+  if (e == hipSuccess) e = prepare_t<Tile64, P, attn_fwd_kernel<Tile64, P>>();
   return e;
+}
+hipError_t attn_fwd_prepare() {
+  const hipError_t e = prepare_all<AttnParams>();
+  return e == hipSuccess ? prepare_all<AttnListParams>() : e;
 }
 
 int attn_fwd_block_m(AttnKernel kernel) { return kernel == AttnKernel::kIndependent128 ? 128 : 256; }
@@ -588,23 +603,33 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   return AttnKernel::kPingPong256;
 }
 
-hipError_t attn_fwd_launch(const AttnParams& p, AttnKernel kernel, int head_dim, int n_cus, int32_t max_keys, hipStream_t stream) {
+template <class P>
+static hipError_t launch_p(const P& p, AttnKernel kernel, int head_dim, int n_cus, int32_t max_keys, hipStream_t stream) {
   const int64_t max_grid = (int64_t)n_cus * attn_fwd_wgs_per_cu(kernel, head_dim);
   const int grid = (int)(p.n_items < max_grid ? p.n_items : max_grid);
   if (kernel != AttnKernel::kIndependent128) {
-    if (head_dim == 128) return launch_t<Tile<128, 8, 64, 2>, attn_fwd_pp_kernel<Tile<128, 8, 64, 2>>>(p, grid, stream);
-    if (head_dim == 64) return launch_t<Tile<64, 8, 64, 2>, attn_fwd_pp_kernel<Tile<64, 8, 64, 2>>>(p, grid, stream);
+    if (head_dim == 128) return launch_t<TilePP128, P, attn_fwd_pp_kernel<TilePP128, P>>(p, grid, stream);
+    if (head_dim == 64) return launch_t<TilePP64, P, attn_fwd_pp_kernel<TilePP64, P>>(p, grid, stream);
   } else {
     // Four ring slots where no compute unit has two items (see the kernel).  Two / four slots, rows x heads: on a chip that is
     // at most half full from 13 key tiles on (700 x 8 14.3 / 14.4, 832 x 8 16.0 / 15.4, 1024 x 8 19.2 / 18.3, 2048 x 3 31.6 /
     // 28.3, 4096 x 4 59 / 53), on a fuller one from 28 on (1024 x 24 21.8 / 22.5, 1500 x 20 31.3 / 32.2, 2048 x 16 39.7 / 39.4,
     // 4096 x 8 70.3 / 66.7, 8192 x 4 133 / 125): below, the longer start of an item weighs more.
     if (head_dim == 128 && p.n_items <= (uint32_t)n_cus && max_keys > 64 * (2 * p.n_items <= (uint32_t)n_cus ? 12 : 27))
-      return launch_t<Tile<128, 4, 64, 1, 4>, attn_fwd_kernel<Tile<128, 4, 64, 1, 4>>>(p, grid, stream);
-    if (head_dim == 128) return launch_t<Tile<128, 4, 64>, attn_fwd_kernel<Tile<128, 4, 64>>>(p, grid, stream);
-    if (head_dim == 64) return launch_t<Tile<64, 4, 64>, attn_fwd_kernel<Tile<64, 4, 64>>>(p, grid, stream);
+      return launch_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>(p, grid, stream);
+    if (head_dim == 128) return launch_t<Tile128, P, attn_fwd_kernel<Tile128, P>>(p, grid, stream);
+    if (head_dim == 64) return launch_t<Tile64, P, attn_fwd_kernel<Tile64, P>>(p, grid, stream);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t attn_fwd_launch(const AttnParams& p, const PackList* list, AttnKernel kernel, int head_dim, int n_cus, int32_t max_keys,
+                           hipStream_t stream) {
+  if (list == nullptr) return launch_p(p, kernel, head_dim, n_cus, max_keys, stream);
+  AttnListParams lp;
+  static_cast<AttnParams&>(lp) = p;
+  lp.list = *list;
+  return launch_p(lp, kernel, head_dim, n_cus, max_keys, stream);
 }
 
 }  // namespace dit

@@ -57,6 +57,30 @@ void plan_build_cross(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, 
   }
 }
 
+bool pack_list_build(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads, int32_t block_m, PackList& list) {
+  list.n = 0;
+  int n = 0;
+  for (int32_t i = 0; i < n_seqs; ++i) {  // insertion sort by descending number of keys, ties in pack order
+    const int32_t q_len = cu_q[i + 1] - cu_q[i], k_len = cu_k[i + 1] - cu_k[i];
+    if (q_len == 0 || k_len == 0) continue;
+    if (n == kPackListSeqs) return false;
+    int pos = n++;
+    for (; pos > 0 && list.seq[pos - 1].kv_len < k_len; --pos) list.seq[pos] = list.seq[pos - 1];
+    list.seq[pos] = PackSeq{0, cu_q[i], q_len, cu_k[i], k_len, 0};
+  }
+  uint64_t items = 0;
+  for (int j = 0; j < n; ++j) {
+    PackSeq& s = list.seq[j];
+    const uint32_t whole = static_cast<uint32_t>(s.q_len / block_m);
+    s.first = static_cast<uint32_t>(items);
+    s.inv_whole = whole > 1 ? static_cast<uint32_t>(((uint64_t{1} << 32) + whole - 1) / whole) : 0;
+    items += (static_cast<uint64_t>(s.q_len) + block_m - 1) / block_m * static_cast<uint64_t>(n_heads);
+    if (items > kPackListItems) return false;
+  }
+  list.n = n;
+  return n > 0;
+}
+
 int plan_cache_victim(const uint64_t* last_use, const uint8_t* pinned, int n) {
   int victim = -1;
   for (int i = 0; i < n; ++i)

@@ -20,6 +20,41 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 16, "WorkItem must be 16 bytes");
 
+// The same list as a formula: the sequences in list order, from which item idx follows (pack_list_item).  A launch of the
+// entry point that allocates nothing whose items all start at once takes it as a kernel argument instead of a list in memory,
+// for packs of at most kPackListSeqs sequences with queries and keys.
+constexpr int kPackListSeqs = 16;
+constexpr uint32_t kPackListItems = 1u << 14;
+struct PackSeq {
+  uint32_t first;      // index of the sequence's first item
+  int32_t q_start, q_len, kv_start, kv_len;
+  uint32_t inv_whole;  // ceil(2^32 / whole query tiles per head), 0 for one tile or none: x / whole = (x * inv_whole) >> 32 for
+                       // x, whole <= kPackListItems (the product's excess over a multiple is under whole, times x under 2^32)
+};
+struct PackList {
+  int32_t n;
+  PackSeq seq[kPackListSeqs];
+};
+
+// Fills `list` for a pack with n_items items; false (list.n = 0) if it has too many sequences or items.
+bool pack_list_build(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads, int32_t block_m, PackList& list);
+
+// Item idx, which belongs to sequence s of the list (the last one with first <= idx), of the list that plan_build_cross
+// makes with one part per sequence.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline WorkItem pack_list_item(const PackSeq& s, uint32_t idx, uint32_t n_heads, int32_t block_m) {
+  const uint32_t local = idx - s.first, whole = static_cast<uint32_t>(s.q_len / block_m), n_whole = whole * n_heads;
+  uint32_t head = local - n_whole, tile = whole;  // the ragged last tiles follow the whole ones of all heads
+  if (local < n_whole) {
+    head = s.inv_whole ? static_cast<uint32_t>((static_cast<uint64_t>(local) * s.inv_whole) >> 32) : local;
+    tile = local - head * whole;
+  }
+  const int32_t m0 = static_cast<int32_t>(tile) * block_m, rows = s.q_len - m0 < block_m ? s.q_len - m0 : block_m;
+  return WorkItem{s.q_start + m0, s.kv_start, s.kv_len, static_cast<int32_t>((static_cast<uint32_t>(rows) << 16) | head)};
+}
+
 // Validate cu_seqlens: returns 0 if ok (cu[0]==0, non-decreasing, n_seqs>=0), else non-zero.
 int plan_validate(const int32_t* cu_seqlens, int32_t n_seqs);
 
