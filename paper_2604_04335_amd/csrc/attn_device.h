@@ -41,6 +41,7 @@
 #include <stdint.h>
 
 #include "attn_fwd.h"
+#include "store_through.h"
 
 namespace dit {
 
@@ -48,8 +49,8 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 typedef __attribute__((address_space(3))) char lds_char;
@@ -782,20 +783,44 @@ __device__ __forceinline__ void store_out(const AttnParams& p, const Lane<T>& L,
                                           float l_run, float m_ref, uint32_t stage) {
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   if (p.part_out != nullptr) {
-    // split-KV: this item saw one chunk of the keys; its normalised result and lse go to the workspace in fp32
-    if (!row_valid) return;
-    const float inv = 1.0f / l_tot;
-    const int64_t rh = ((int64_t)it.part * p.part_rows + it.q_start + qrow) * p.n_heads + it.head;
-    float* optr = p.part_out + rh * T::D + L.hh * 4;
+    // split-KV: this item saw one chunk of the keys; its normalised result and lse go to the workspace in fp32, half a row
+    // at a time through the staging area and out as whole halves, like the bf16 rows below; written through the L2, as
+    // the merge kernel reads them next on other XCDs.  us of the call, stored from the accumulator layout (16 bytes of each
+    // of 32 rows per instruction) / as half rows, left dirty in the L2 / written through: 4951 rows x 3 heads, four chunks
+    // 48.4 / 47.2 / 46.5;  2500 x 3 26.1 / 25.5 / 23.8;  16384 x 1 121.0 / 119.7 / 118.5;  1570 x 5 20.2 / 19.8 / 18.9.
+    typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+    constexpr int CH = T::D / 8;     // 16-byte chunks of half a row
+    constexpr int RPS = 64 / CH;     // half rows per store instruction
+    const float inv = 1.0f / l_tot;  // finite for rows past the end of a ragged tile too, which are not stored
+    const int64_t rh0 = ((int64_t)it.part * p.part_rows + it.q_start) * p.n_heads + it.head;
+    const int ch = L.lane & (CH - 1), r0 = L.lane / CH, row0 = L.wave * 32 + r0;
+    float* const optr = p.part_out + (rh0 + (int64_t)row0 * p.n_heads) * T::D + ch * 4;
+    const int n_valid = it.q_rows - row0;
 #pragma unroll
-    for (int db = 0; db < T::NDB; ++db)
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-        *reinterpret_cast<f32x4*>(optr + 32 * db + 8 * g) =
-            f32x4{o[db][4 * g + 0] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv};
+      for (int b = 0; b < T::NDB / 2; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int db = half * (T::NDB / 2) + b;
+          const f32x4 f = {o[db][4 * g + 0] * inv, o[db][4 * g + 1] * inv, o[db][4 * g + 2] * inv, o[db][4 * g + 3] * inv};
+          *(lds_u32x4*)(uintptr_t)(stage + (uint32_t)(L.l32 * (CH * 16) + (((8 * b + 2 * g + L.hh) ^ (L.l32 & (CH - 1))) * 16))) =
+              __builtin_bit_cast(u32x4, f);
+        }
+      asm volatile("" ::: "memory");  // LDS serves a wavefront's instructions in order
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = 0; i < 32 / RPS; ++i) {
+        const int r = r0 + i * RPS;
+        const u32x4 w = *(lds_u32x4*)(uintptr_t)(stage + (uint32_t)(r * (CH * 16) + ((ch ^ (r & (CH - 1))) * 16)));
+        if (i * RPS < n_valid)
+          store_through(reinterpret_cast<u32x4*>(optr + (int64_t)(i * RPS) * p.n_heads * T::D + half * (T::D / 2)), w);
       }
-    if (L.hh == 0) p.part_lse[rh] = 0.69314718055994530942f * (m_ref * p.c_log2 + __builtin_amdgcn_logf(l_tot));
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (row_valid && L.hh == 0)
+      p.part_lse[rh0 + (int64_t)qrow * p.n_heads] = 0.69314718055994530942f * (m_ref * p.c_log2 + __builtin_amdgcn_logf(l_tot));
     return;
   }
   {
