@@ -484,7 +484,7 @@ __device__ __forceinline__ uint64_t tile_softmax(f32x16 (&s)[T::NKB], int hh, Ta
   const int tail_lo = rows.lo - 4 * hh;
   const unsigned tail_n = (unsigned)(rows.hi - rows.lo);
   auto dead = [&](int kb, int i) { return (unsigned)(32 * kb + 8 * (i >> 2) + (i & 3) - tail_lo) >= tail_n; };
-  if (TAIL) {
+  if (TAIL && rows.hi - rows.lo != T::BN) {  // a last tile that is whole skips the mask: 1024 x 8, D 128 17.6 / 17.1 us
 #pragma unroll
     for (int kb = 0; kb < T::NKB; ++kb)
 #pragma unroll
@@ -764,6 +764,35 @@ __device__ __forceinline__ void load_q(const AttnParams& p, const Lane<T>& L, co
 #pragma unroll
   for (int ks = 0; ks < T::NKS; ++ks) {
     u32x4 w = *reinterpret_cast<const u32x4*>(qptr + ks * 32);
+    if (p.negate) w ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+    qf[ks] = __builtin_bit_cast(bf16x8, w);
+  }
+}
+
+// The same through LDS: this wavefront's 32 rows as direct loads of whole rows into 32 * ROW_B bytes at LDS byte qs, in the
+// K tile's chunk order (q_rows_load), and, once they have landed, into registers (q_rows_read).  A register load touches 32
+// rows with 32 bytes each, four times the cache-line requests: see the kernel that uses this for what it measured.
+// Rows past the end of a ragged query tile are copies of its last row.
+template <class T>
+__device__ __forceinline__ void q_rows_load(const AttnParams& p, const Lane<T>& L, const ItemU& it, int64_t row_stride_b,
+                                            int64_t head_off, uint32_t qs) {
+  const char* base = static_cast<const char*>(p.q) + (int64_t)it.q_start * row_stride_b + head_off;  // scalar
+  constexpr int N = 32 / T::RPI;
+  const int r0 = L.lane / T::CPR, pos = L.lane % T::CPR;
+  const bool full = L.wave * 32 + 32 <= it.q_rows;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int r = i * T::RPI + r0;  // of the wavefront's rows
+    int row = L.wave * 32 + r;      // of the item's
+    if (!full) row = row < it.q_rows ? row : it.q_rows - 1;
+    lds_dma_16(base, (uint32_t)row * (uint32_t)row_stride_b + (uint32_t)((pos ^ T::swz_k(r)) * 16), qs + i * 1024);
+  }
+}
+template <class T>
+__device__ __forceinline__ void q_rows_read(const AttnParams& p, const Lane<T>& L, uint32_t qs, bf16x8 (&qf)[T::NKS]) {
+#pragma unroll
+  for (int ks = 0; ks < T::NKS; ++ks) {
+    u32x4 w = __builtin_bit_cast(u32x4, *(lds_bf16x8*)(uintptr_t)(qs + (uint32_t)(L.l32 * T::ROW_B + (((2 * ks + L.hh) ^ T::swz_k(L.l32)) * 16))));
     if (p.negate) w ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
     qf[ks] = __builtin_bit_cast(bf16x8, w);
   }

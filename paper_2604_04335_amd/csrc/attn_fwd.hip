@@ -87,14 +87,19 @@ attn_fwd_kernel(P p) {
 #pragma unroll
       for (int i = 0; i < T::LPT; ++i) lds_dma_16(base, vvoff[i], dst + i * T::NWAVES * 1024);
     };
-    bf16x8 qf[T::NKS];
+    // Q goes through slots that the first tiles do not need yet: two wavefronts' rows in K slot 1, two in V slot 1.  As
+    // register loads (256 cache-line requests a wavefront instead of 64) the first loads of an item of 512 keys took 3 100
+    // cycles of 31 000 to issue.  us: 1024 x 8, D 128 18.2 / 17.6, D 64 12.57 / 12.43;  46618 x 24 against 512 keys, D 128
+    // 342 / 336, 226 keys 221 / 214.  (In the ping-pong kernel, whose buffers are all busy then, not worth a buffer.)
+    constexpr int PER = T::TILE_B / (32 * T::ROW_B);  // wavefronts per slot
+    static_assert(T::NWAVES == 2 * PER, "rows of four wavefronts in two slots");
+    const uint32_t spare = (uint32_t)(uintptr_t)smem + (wave < PER ? T::K_OFF : T::V_OFF) + T::TILE_B + (uint32_t)(wave % PER) * (32 * T::ROW_B);
     {
       const Lane<T> L = fresh_lane();
+      q_rows_load<T>(p, L, X.it, row_stride_b, X.head_off, spare);
       tile_load_one<T>(X.kbase, row_stride_b, 0, kv_len, L.lrow, L.kcol, kvoff[0], smem, T::K_OFF, wave);
-      load_q<T>(p, L, X.it, row_stride_b, X.head_off, X.qrow, qf);
       tile_load_one<T>(X.vbase, row_stride_b, 0, kv_len, L.lrow, L.vcol, vvoff[0], smem, T::V_OFF, wave);
     }
-    if (nt > 1) load_k(1);
 
     f32x16 o[T::NDB];
 #pragma unroll
@@ -110,9 +115,12 @@ attn_fwd_kernel(P p) {
 
     if (nt == 1 && tid == 0 && !one_round) s_item[par] = take_item(p);  // visible after the barrier below
     wait_loads();
+    bf16x8 qf[T::NKS];
+    q_rows_read<T>(p, fresh_lane(), spare, qf);
+    wg_barrier();
+    if (nt > 1) load_k(1);
     if (NB > 2 && nt > 2) load_k(2);
     if (NB > 2 && nt > 1) load_v(1);
-    wg_barrier();
     mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, sa);
     if (nt > 1) mx = tile_max<T>(sa);
     // Step t: S(t) is in sc; leaves S(t+1) in sn.  Every PER_BAR steps there is a barrier, behind which K(t+1) and V(t) (with
@@ -205,16 +213,12 @@ attn_fwd_kernel(P p) {
     mfma_stream<T, true, 0, 0, kPrefetch>(smem, va, ka, pb, qf, o, sa);
     l_run += row_sum<T>(pb);
 
-    // The rows are staged where nobody reads or loads any more behind the barrier of the last tile: in the K ring, and for
-    // what it does not hold in the V slots of other tiles than the last.
+    // The rows are staged in the K ring, which nobody reads or loads into behind the barrier of the last tile, or, with one
+    // tile and no such barrier, where Q was.
     int qrow = L.wave * 32 + L.l32;
     const bool row_valid = qrow < X.it.q_rows;
     if (!row_valid) qrow = X.it.q_rows - 1;
-    constexpr int PER = T::TILE_B / (32 * T::ROW_B);  // wavefronts per slot
-    const int sl = wave / PER;
-    const uint32_t stage = (uint32_t)(uintptr_t)smem + (uint32_t)(wave % PER) * (32 * T::ROW_B) +
-                           (nt > 1 ? T::K_OFF + sl * T::TILE_B : sl + 1 < NB ? T::K_OFF + (sl + 1) * T::TILE_B : T::V_OFF + T::TILE_B);
-    static_assert(T::NWAVES / PER <= NB, "staging area");
+    const uint32_t stage = nt > 1 ? (uint32_t)(uintptr_t)smem + T::K_OFF + (uint32_t)wave * (32 * T::ROW_B) : spare;
     store_out<T>(p, L, X.it, row_stride_b, X.head_off, qrow, row_valid, o, l_run, m_ref, stage);
     if (one_round) break;
     wg_barrier();  // the next item's first loads overwrite ring slot 0
