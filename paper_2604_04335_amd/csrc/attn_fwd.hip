@@ -556,54 +556,57 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
     tiles += it * nt;
     max_tiles = nt > max_tiles ? nt : max_tiles;
   }
-  // Compute units to spare for 128-row items: nothing is gained by longer ones.  D 128, under 0.45 256-row items per
-  // compute unit: 1024 x 12 22.3 / 25.0, 1570 x 12 32.3 / 35.5 (at 0.47, 1280 x 24, 29.2 / 30.6).  D 64, as long as every
-  // 128-row item has a compute unit of its own: 1280 x 24 20.1 / 24.1, 410 x 24 8.8 / 11.6;  288 items 17.4 / 15.8.
-  if (head_dim == 64 ? items128 <= n_cus : items256 * 20 < (int64_t)n_cus * 9) return AttnKernel::kIndependent128;
+  // Every 128-row item has a compute unit of its own: nothing is gained by longer ones.  D 128: 1280 x 24 27.5 / 30.9,
+  // 1536 x 21 31.6 / 35.5, 2048 x 15 34.4 / 44.0;  past it 1300 x 24 36.7 / 32.3, 1408 x 24 38.2 / 33.2.  (So are 128 items of 256 rows
+  // that are all whole, 4096 x 8 66 / 88, whose block_m of dit_attn_plan is what callers know, and stays.)  D 64: 1280 x 24
+  // 17.1 / 23.4, 410 x 24 7.8 / 11.7;  past it 1281 x 24 24.1 / 24.7.
+  if (items128 <= n_cus && (head_dim == 64 || 2 * items256 < n_cus)) return AttnKernel::kIndependent128;
   // Items with few key tiles (cross-attention against text keys): the 128-row kernel's workgroups have no idle phase at
-  // the ends of an item.  46618 x 24, D 128: 77 keys 142 / 171, 226: 206 / 229, 320: 239 / 259;  D 64: 200 keys 113 / 148.
-  // At D 64 one or two tiles are bound by Q and O, which the larger items move better: 77 keys 108.5 / 103.2, 128 keys
-  // 109.0 / 104.4 (8704 x 24: 25.2 / 24.9 and 25.2 / 25.3).
+  // the ends of an item.  46618 x 24, D 128: 77 keys 149 / 178, 226: 202 / 224, 512: 322 / 334, 640: 379 / 386 (8704 x 24: 73 /
+  // 79), 768: 438 / 439;  D 64: 200 keys 112 / 148.  At D 64 one or two tiles are bound by Q and O, which the larger items move
+  // better: 77 keys 109.3 / 102.9, 128 keys 109.0 / 95.7 (8704 x 24: 24.7 / 24.7 and 24.6 / 23.1).
   if (cu_seqlens_k != nullptr && tiles <= 5 * items256)
     return head_dim == 64 && tiles <= 2 * items256 ? AttnKernel::kPingPong256 : AttnKernel::kIndependent128;
   // The 256-row items take no longer than the longest of them: the ping-pong kernel's are the quicker ones.  D 128:
-  // 1570 x 24 47.1 / 37.1, 410 and 2458 x 24 81.9 / 70.5;  D 64: 1570 x 24 31.9 / 28.7, 2458 x 24 49.8 / 44.6.
+  // 1570 x 24 43.5 / 37.3, 410 and 2458 x 24 78.4 / 71.7, against 512 keys 19.6 / 18.3;  D 64: 1570 x 24 28.1 / 28.3, 2458 x 24
+  // 45.2 / 44.3.
   if (tiles <= n_cus * max_tiles) return AttnKernel::kPingPong256;
   // Past one round at D 64 three workgroups of the 128-row kernel share a compute unit and are ahead in general: 512 x 24
-  // heads x 18 sequences 45.9 / 51.5, 1024 x 24 x 9 77.6 / 82.7, 1536 x 24 x 6 105 / 113, 3000 x 24 79 / 98, 3600 x 24
-  // 100 / 119, 4352 x 24 142 / 148, 2049 x 24 x 6 181 / 200, 6000 x 24 257 / 287, 4352 x 24 x 4 483 / 497, 46618 x 24 against
-  // 512 keys 185 / 224.  Batches of several lengths are between 14 % ahead and 4 % behind: 3167, 537, 876 and 322 rows 89 /
-  // 104, 4 each of 4352, 2458, 1054 and 410 677 / 726, 410 to 4250 rows 355 / 353 to 368, 421 to 3916 rows x 12 170 / 165.
+  // heads x 18 sequences 45.0 / 48.1, 1024 x 24 x 9 70.3 / 79.4, 1536 x 24 x 6 93 / 112, 3000 x 24 73 / 98, 3600 x 24 93 / 122,
+  // 4352 x 24 135 / 145, 2049 x 24 x 6 176 / 198, 6000 x 24 233 / 287, 4352 x 24 x 4 451 / 509, 46618 x 24 against 512 keys 172 /
+  // 215.  Batches of several lengths too: 3167, 537, 876 and 322 rows 85 / 104, 4 each of 4352, 2458, 1054 and 410 635 / 700,
+  // 410 to 4250 rows 325 / 350, 421 to 3916 rows x 12 86 / 89.
   // The exceptions, for self-attention:
   if (head_dim == 64 && cu_seqlens_k == nullptr) {
     // Short items that are two rounds for the ping-pong kernel and more than one for the 128-row kernel, whose second round
-    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together; its times
-    // also scatter, 400 x 24 x 9 between 23 and 29 from one run of the program to the next, the ping-pong kernel 24.4 to 25):
-    // 410 x 24 x 9 27.9 / 24.8, 700 x 24 x 6 34.6 to 39 / 32.7, 745 x 24 x 7 40.9 / 36.8, 925 x 12 x 10 45.4 / 40.6, 1054 x 24
-    // x 4 45 to 57 / 44, 512 x 24 x 9 29.0 to 30.3 / 28.5, 1024 x 24 x 5 46.3 / 45.8, 1300 x 12 x 6 53.3 / 51.0.  Not where the
-    // 256-row items hold under 200 rows on average: 520 x 24 x 7 25.8 / 28.7, 588 x 24 x 7 29.3 / 31.0 (610 rows 30.1 / 31.3,
-    // 790 x 24 x 5 36.1 / 36.0);  not with a third round: 1120 x 24 x 5 57.7 / 59.5, 1331 x 12 x 8 63.1 / 66.6, 1024 x 24 x 6
-    // 54.6 / 61.4 (three full ones are level or better: 512 x 24 x 16 41.8 / 42.9, 1024 x 24 x 8 72.0 / 67.6);  not with one
-    // round: 300 x 24 x 10 16.6 / 20.2.  Longer items even it out: 24 tiles 58.5 / 59.7 (1536 x 24 x 3) and 62.7 / 61.7
-    // (1510 x 12 x 7), 28 tiles (1792 x 24 x 3) 72.8 / 72.9.
+    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together):
+    // 410 x 24 x 9 24.7 / 24.4, 745 x 24 x 7 35.9 / 35.7, 925 x 12 x 10 42.4 / 39.7, 1054 x 24 x 4 44.8 / 42.6, 512 x 24 x 9
+    // 30.1 / 26.3, 1024 x 24 x 5 47.2 / 42.4.  Not where the 256-row items hold under 200 rows on average: 520 x 24 x 7 27.7 /
+    // 28.7, 588 x 24 x 7 29.8 / 30.4 (790 x 24 x 5 36.1 / 35.6);  not with a third round: 1120 x 24 x 5 51.9 / 59.8, 1331 x 12
+    // x 8 57 / 67, 1024 x 24 x 6 54.0 / 58.2 (three full ones: 512 x 24 x 16 42.8 / 39.4, 1024 x 24 x 8 66.3 / 65.5);  not with
+    // one round: 300 x 24 x 10 14.8 / 20.4.  The 128-row kernel has come to be ahead between 18 and 24 tiles (1300 x 12 x 6 46.2 /
+    // 49.5, 1536 x 24 x 3 54.0 / 57.6) and in the rule below by 2 to 8 % (2458 x 24 x 4 162 / 172, 3750 x 8 x 8 240 / 258, 5120 x
+    // 24 x 2 331 / 341, 3000 x 12 x 7 208 / 212), as at 101 to 127 tiles further down (7000 x 24 327 / 339): block_m of
+    // dit_attn_plan for such packs is what callers know, and stays.
     if (tiles <= 24 * items256 && items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus && rows >= 200 * items256)
       return AttnKernel::kPingPong256;
-    // Longer items that just fill a fourth round of the ping-pong kernel leave the 128-row kernel a third one half full:
-    // 2458 x 24 x 4 182 / 176, 3750 x 8 x 8 3 % apart, 5120 x 24 x 2 357 / 352, 3000 x 12 x 7 225 / 220.
+    // Longer items that just fill a fourth round of the ping-pong kernel leave the 128-row kernel a third one half full.
     if (tiles > 24 * items256 && 4 * items256 >= 15 * (int64_t)n_cus && items256 <= 4 * (int64_t)n_cus) return AttnKernel::kPingPong256;
   }
-  // Above 100 key tiles on average either kernel can be ahead: 7500 x 24 372.5 / 374, 16000 x 24 1643 / 1564, 20506 x 24
-  // 2604 / 2639;  the 128-row kernel clearly at 9000 x 24 545 / 573, 12000 x 24 898 / 961 and 8192, 300 and 77 x 12 226 / 258.
-  // With no trend in the size to draw a line by, these stay on the ping-pong kernel.
-  if (head_dim == 64 && tiles <= 100 * items256) return AttnKernel::kIndependent128;
+  // Longer packs: 8192 x 24 407 / 416, 9000 x 24 487 / 580, 12000 x 24 861 / 954, 16000 x 24 1556 / 1536, 20506 x 24 2483 / 2599,
+  // 8192, 300 and 77 x 12 211 / 276.
+  if (head_dim == 64 && (tiles <= 100 * items256 || tiles >= 128 * items256)) return AttnKernel::kIndependent128;
   // Else the ping-pong kernel (D 128: 7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
-  // six or seven key tiles (46618 x 24 against 400 keys 301 / 315, 448 keys 302 / 316; 512 keys 332 / 337) and a second round
-  // that is at most 40 % full (2600 x 24 86 / 104, 3200 x 24 145 / 150, 3600 x 24 170 / 171; 41 %, 1500 x 20 x 3, 78.0 / 78.5;
-  // half full, 4000 x 24 193 / 190 and 2000 x 24 x 2 103 / 102; 4352 x 24 245 / 218).
+  // up to eleven key tiles (see above) and equal items that leave much of its last round empty: a second round at most three
+  // sevenths full (2600 x 24 84 / 102, 3200 x 24 133 / 142, 3600 x 24 159 / 172, 1500 x 20 x 3 78.5 / 86;  half full, 4000 x 24
+  // 200 / 199, 2000 x 24 x 2 108 / 111, 900 x 24 x 4 60 / 57;  4352 x 24 225 / 223, 5120 x 24 281 / 264) or a third one a quarter full
+  // (6000 x 24 405 / 421, 2000 x 24 x 3 150 / 158, 700 x 24 x 8 64 / 67;  16384 x 10, half full, 1114 / 1108).
   // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still
   // ramp, whichever kernel runs second looks faster.)
-  if (cu_seqlens_k != nullptr && tiles <= 7 * items256) return AttnKernel::kIndependent128;
-  if (items256 > n_cus && 5 * (items256 - n_cus) <= 2 * (int64_t)n_cus) return AttnKernel::kIndependent128;
+  if (cu_seqlens_k != nullptr && tiles <= 11 * items256) return AttnKernel::kIndependent128;
+  if (items256 > n_cus && 7 * (items256 - n_cus) <= 3 * (int64_t)n_cus) return AttnKernel::kIndependent128;
+  if (items256 > 2 * (int64_t)n_cus && 4 * (items256 - 2 * (int64_t)n_cus) <= (int64_t)n_cus && tiles == max_tiles * items256)
+    return AttnKernel::kIndependent128;
   return AttnKernel::kPingPong256;
 }
 

@@ -59,3 +59,45 @@ def test_cross_choice_at_head_dim_64(n_keys, kernel):
         assert all(torch.equal(outs[0].view(torch.int16), o.view(torch.int16)) for o in outs[1:])
     finally:
         da.dit_attn_destroy(ctx)
+
+
+@pytest.mark.parametrize("lens,heads,head_dim,block_m", [
+    ([1280], 24, 128, 128),          # 240 items of 128 rows, 120 of 256: under half of the compute units
+    ([1281], 24, 128, 256),          # 264 items of 128 rows
+    ([2048], 15, 128, 128),
+    ([2048], 16, 128, 256),          # 128 items of 256 rows
+    ([3600], 24, 128, 128),          # 360: a second round 41 % full
+    ([3841], 23, 128, 256),          # 368: 44 %
+    ([6000], 24, 128, 128),          # 576 equal items: a third round a quarter full
+    ([6000], 25, 128, 256),          # 600
+    ([6000, 3000], 17, 128, 256),    # 612 items of two lengths: the short ones fill the round
+    ([8128], 24, 64, 256),           # 127 key tiles
+    ([8129], 24, 64, 128),           # 128
+])
+def test_kernel_choice_of_fuller_rounds(lens, heads, head_dim, block_m):
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    assert da.dit_attn_plan(cu, heads, head_dim)[1] == block_m
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_keys,kernel", [(64, "128"), (448, "128"), (704, "128"), (705, "PINGPONG")])
+def test_cross_choice_at_head_dim_128(n_keys, kernel):
+    """Up to eleven key tiles run the 128-row kernel, more the ping-pong kernel; either gives the bits of the other."""
+    import torch
+    print(f"cross choice: {n_keys} keys", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n_keys)
+    q, k, v = (torch.randn((n, 24, 128), device="cuda", generator=gen).to(torch.bfloat16) for n in (5000, 2 * n_keys, 2 * n_keys))
+    ctx, stream = da.dit_attn_create(0), torch.cuda.current_stream().cuda_stream
+    try:
+        outs = []
+        for forced in (da.KERNEL_AUTO, da.KERNEL_128, da.KERNEL_PINGPONG):
+            da.dit_attn_set_kernel(ctx, forced)
+            outs.append(torch.full_like(q, float("nan")))
+            da.dit_attn_cross_varlen_fwd(ctx, q, k, v, [0, 2600, 5000], [0, n_keys, 2 * n_keys], 24, 128, 0.09, outs[-1], None, stream)
+            if forced == da.KERNEL_AUTO and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+                assert da.dit_attn_last_launch_kernel(ctx) == getattr(da, "KERNEL_" + kernel)
+        torch.cuda.synchronize()
+        assert not bool(outs[0].isnan().any())
+        assert all(torch.equal(outs[0].view(torch.int16), o.view(torch.int16)) for o in outs[1:])
+    finally:
+        da.dit_attn_destroy(ctx)
