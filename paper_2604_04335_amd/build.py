@@ -18,6 +18,7 @@ PROBE_SOURCES = ["probe/mfma_ceiling.hip"]
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=8",  # leading scalar kernel arguments arrive in scalar registers
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

@@ -31,7 +31,7 @@ constexpr int kWavesPerSimd = T::NBUF > 2 ? 2 : kWgsPerCu128<T::D>;
 
 template <class T, class P>
 __global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(kWavesPerSimd<T>, kWavesPerSimd<T>)))
-attn_fwd_kernel(P p) {
+attn_fwd_kernel(const WorkItem* items, P p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs the kernel's name only, and fails on the second instance of a body
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
   lds_char* smem = (lds_char*)smem_generic;
@@ -71,7 +71,7 @@ attn_fwd_kernel(P p) {
 
   while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
-    const ItemCtx<T> X = begin_item<T, P>(p, fresh_lane(), item_idx, row_stride_b);
+    const ItemCtx<T> X = begin_item<T, P>(p, items, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;
 
     // Tile ti -> its ring slot.  Only for sequences of two tiles or more, whose tiles are all loaded whole.
@@ -114,7 +114,10 @@ attn_fwd_kernel(P p) {
     fresh_lane().operand_addrs((uint32_t)(uintptr_t)smem, (uint32_t)(uintptr_t)smem, ka, va);
 
     if (nt == 1 && tid == 0 && !one_round) s_item[par] = take_item(p);  // visible after the barrier below
-    wait_loads();
+    if (nt > 1)
+      wait_loads_but<T::LPT>();  // V(0) is awaited with K(1), before step 0
+    else
+      wait_loads();
     bf16x8 qf[T::NKS];
     q_rows_read<T>(p, fresh_lane(), spare, qf);
     wg_barrier();
@@ -254,7 +257,7 @@ attn_fwd_kernel(P p) {
 // ---------------------------------------------------------------------------------------------
 template <class T, class P>
 __global__ void __attribute__((amdgpu_flat_work_group_size(T::NT, T::NT), amdgpu_waves_per_eu(2, 2)))
-attn_fwd_pp_kernel(P p) {
+attn_fwd_pp_kernel(const WorkItem* items, P p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass needs the kernel's name only, and fails on the second instance of a body
   static_assert(T::NWAVES == 8 && T::SUBS == 2, "two groups of four wavefronts, two tiles per phase");
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
@@ -294,7 +297,7 @@ attn_fwd_pp_kernel(P p) {
 
   while (item_idx < p.n_items) {
     par ^= 1;  // the next index goes to s_item[par], see below
-    const ItemCtx<T> X = begin_item<T, P>(p, fresh_lane(), item_idx, row_stride_b);
+    const ItemCtx<T> X = begin_item<T, P>(p, items, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;  // nt: 64-key tiles
     const int npairs = (nt + 1) >> 1;
 
@@ -493,7 +496,7 @@ attn_fwd_pp_kernel(P p) {
 }
 
 // The LDS limit of a kernel is set once per device (its first use there also loads the kernel's code).
-template <class T, class P, void (*KERNEL)(P)>
+template <class T, class P, void (*KERNEL)(const WorkItem*, P)>
 static hipError_t prepare_t() {
   static bool attr_set[16] = {};
   int dev = 0;
@@ -507,11 +510,11 @@ static hipError_t prepare_t() {
   return hipSuccess;
 }
 
-template <class T, class P, void (*KERNEL)(P)>
+template <class T, class P, void (*KERNEL)(const WorkItem*, P)>
 static hipError_t launch_t(const P& p, int grid, hipStream_t stream) {
   const hipError_t e = prepare_t<T, P, KERNEL>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(T::NT), T::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(T::NT), T::LDS_BYTES, stream, p.items, p);
   return hipGetLastError();
 }
 
