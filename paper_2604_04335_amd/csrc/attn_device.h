@@ -69,13 +69,14 @@ constexpr int kPrefetch = 4;
 
 // BN keys form one tile: the unit of the softmax (one reference-value decision per row and tile) and of the loads.
 // A K or V buffer holds SUBS consecutive tiles; the ping-pong kernel works through SUBS = 2 tiles per phase.
-template <int D_, int NWAVES_, int BN_, int SUBS_ = 1, int NBUF_ = 2>
+template <int D_, int NWAVES_, int BN_, int SUBS_ = 1, int NBUF_ = 2, int EVERY_ = 0>
 struct Tile {
   static constexpr int D = D_;
   static constexpr int NWAVES = NWAVES_;
   static constexpr int BN = BN_;
   static constexpr int SUBS = SUBS_;
   static constexpr int NBUF = NBUF_;               // K and V buffers each
+  static constexpr int EVERY = EVERY_;             // 128-row kernel: loads of a step behind every so many MFMAs, 0: all at its start
   static constexpr int NT = NWAVES * 64;           // threads
   static constexpr int BM = NWAVES * 32;           // query rows per workgroup
   static constexpr int ROW_B = D * 2;              // bytes of one K/V row of one head

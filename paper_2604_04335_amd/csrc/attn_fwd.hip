@@ -18,10 +18,12 @@ namespace dit {
 // D 128 88.5 / 69.6.
 //
 // Two K and V ring slots let several workgroups share a compute unit: three at head dimension 64, two at 128 (a third
-// wavefront per SIMD at 64, in 165 registers, fills more of the issue slots: image batch 344 with two, 332 with three).
-// Four slots are for workgroups that have a compute unit to themselves (head dimension 128): a barrier every second tile,
-// and the loads spread over a tile instead of a burst in which the four wavefronts wait for one another on the way to
-// memory.  16384 x 1 216 / 187, 4951 x 3 69.6 / 62.0, 1024 x 8 19.1 / 18.4; at 64, with half the loads, 137 / 136.
+// wavefront per SIMD at 64, in 159 registers, fills more of the issue slots: image batch 344 with two, 332 with three).
+// A step's direct loads stand behind its first MFMAs, one each (every second one at 128): issued in a burst behind the
+// barrier, the wavefronts wait for one another on the compute unit's path to memory.  us, burst / spread: 3600 x 24, D 128
+// 161 / 149, 46618 x 24 against 512 keys 323 / 318, 16384 x 1, D 64 136.8 / 134.7, image batch 328 / 326.
+// Four slots are for workgroups that have a compute unit to themselves (head dimension 128; see launch_p): a barrier every
+// second tile.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 constexpr int kWgsPerCu128 = D == 64 ? 3 : 2;
@@ -133,8 +135,8 @@ attn_fwd_kernel(const WorkItem* items, P p) {
     constexpr int PER_BAR = NB / 2;
     const char* kp = X.kbase + (PER_BAR + 1) * tile_stride_b;
     const char* vp = X.vbase + PER_BAR * tile_stride_b;
-    constexpr bool SPREAD = NB > 2;
-    constexpr int NSLOT = T::NQK + T::NPV, NLOAD = 2 * PER_BAR * T::LPT, EVERY = NSLOT / NLOAD;
+    constexpr int NLOAD = 2 * PER_BAR * T::LPT, EVERY = T::EVERY;
+    static_assert(EVERY * NLOAD <= T::NQK + T::NPV, "a step's loads fit its slots");
     auto step = [&](auto uc, auto mainc, f32x16(&sc)[T::NKB], f32x16(&sn)[T::NKB], int t) {
       constexpr int U = decltype(uc)::value;  // t % UNROLL in the main loop, t % 2 behind it
       constexpr bool MAIN = decltype(mainc)::value;
@@ -161,7 +163,7 @@ attn_fwd_kernel(const WorkItem* items, P p) {
             if (t + PER_BAR + n < nt) load_v(t + PER_BAR + n);
           }
         }
-      } else if constexpr (BAR && !SPREAD) {
+      } else if constexpr (BAR && EVERY == 0) {
         static_for<0, NLOAD>(load_i);
       }
       raise_reference<T>(mx, c, o, m_ref, l_run);
@@ -169,7 +171,9 @@ attn_fwd_kernel(const WorkItem* items, P p) {
       tile_step<T, MAIN ? (U + 1) % NB * T::TILE_B : 0, MAIN ? U % NB * T::TILE_B : 0, kPrefetch>(
           va, ka, pb, qf, o, sc, sn, c, mc, mx, [&](auto jc) {
             constexpr int J = decltype(jc)::value;
-            if constexpr (MAIN && BAR && SPREAD && J % EVERY == EVERY / 2 && J / EVERY < NLOAD) load_i(IC<J / EVERY>{});
+            if constexpr (MAIN && BAR && EVERY != 0) {
+              if constexpr (J % EVERY == EVERY / 2 && J / EVERY < NLOAD) load_i(IC<J / EVERY>{});
+            }
           });
       if constexpr (MAIN) {
         if constexpr (BAR) {
@@ -520,15 +524,17 @@ static hipError_t launch_t(const P& p, int grid, hipStream_t stream) {
 
 using TilePP128 = Tile<128, 8, 64, 2>;
 using TilePP64 = Tile<64, 8, 64, 2>;
-using Tile128 = Tile<128, 4, 64>;
-using Tile128Deep = Tile<128, 4, 64, 1, 4>;
-using Tile64 = Tile<64, 4, 64>;
+using Tile128 = Tile<128, 4, 64, 1, 2, 2>;
+using Tile128Burst = Tile<128, 4, 64>;
+using Tile128Deep = Tile<128, 4, 64, 1, 4, 2>;
+using Tile64 = Tile<64, 4, 64, 1, 2, 1>;
 
 template <class P>
 static hipError_t prepare_all() {
   hipError_t e = prepare_t<TilePP128, P, attn_fwd_pp_kernel<TilePP128, P>>();
   if (e == hipSuccess) e = prepare_t<TilePP64, P, attn_fwd_pp_kernel<TilePP64, P>>();
   if (e == hipSuccess) e = prepare_t<Tile128, P, attn_fwd_kernel<Tile128, P>>();
+  if (e == hipSuccess) e = prepare_t<Tile128Burst, P, attn_fwd_kernel<Tile128Burst, P>>();
   if (e == hipSuccess) e = prepare_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>();
   if (e == hipSuccess) e = prepare_t<Tile64, P, attn_fwd_kernel<Tile64, P>>();
   return e;
@@ -621,12 +627,18 @@ static hipError_t launch_p(const P& p, AttnKernel kernel, int head_dim, int n_cu
     if (head_dim == 128) return launch_t<TilePP128, P, attn_fwd_pp_kernel<TilePP128, P>>(p, grid, stream);
     if (head_dim == 64) return launch_t<TilePP64, P, attn_fwd_pp_kernel<TilePP64, P>>(p, grid, stream);
   } else {
-    // Four ring slots where no compute unit has two items (see the kernel).  Two / four slots, rows x heads: on a chip that is
-    // at most half full from 13 key tiles on (700 x 8 14.3 / 14.4, 832 x 8 16.0 / 15.4, 1024 x 8 19.2 / 18.3, 2048 x 3 31.6 /
-    // 28.3, 4096 x 4 59 / 53), on a fuller one from 28 on (1024 x 24 21.8 / 22.5, 1500 x 20 31.3 / 32.2, 2048 x 16 39.7 / 39.4,
-    // 4096 x 8 70.3 / 66.7, 8192 x 4 133 / 125): below, the longer start of an item weighs more.
-    if (head_dim == 128 && p.n_items <= (uint32_t)n_cus && max_keys > 64 * (2 * p.n_items <= (uint32_t)n_cus ? 12 : 27))
-      return launch_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>(p, grid, stream);
+    // Where no compute unit has two items, D 128, us with two slots and a step's loads spread / at its start / with four slots:
+    //   at most half of the compute units busy  448 x 8 9.4 / 10.0 / 10.3,  832 x 8 13.7 / 14.9 / 14.3,  1024 x 8 17.2 / 17.9 /
+    //     17.0,  1280 x 10 20.6 / 21.3 / 20.0,  2048 x 3 26.9 / 30.1 / 27.0,  4096 x 4 51.2 / 56.8 / 50.2: four from 16 tiles on;
+    //   more of them  448 x 40 10.9 / 11.0 / 12.0,  700 x 24 14.7 / 14.8 / 15.7,  900 x 24 19.4 / 18.8 / 20.2,  1024 x 24 21.5 /
+    //     20.4 / 21.7,  1152 x 24 23.3 / 22.8 / 24.4,  1280 x 24 25.4 / 25.3 / 26.4,  1792 x 17 30.8 / 32.5 / 31.3,  3584 x 8 52.2 /
+    //     55.7 / 52.3: the loads at the start between 12 and 19 tiles (why is not known).
+    if (head_dim == 128 && p.n_items <= (uint32_t)n_cus) {
+      const bool half = 2 * p.n_items <= (uint32_t)n_cus;
+      if (half && max_keys > 64 * 15) return launch_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>(p, grid, stream);
+      if (!half && max_keys > 64 * 11 && max_keys <= 64 * 19)
+        return launch_t<Tile128Burst, P, attn_fwd_kernel<Tile128Burst, P>>(p, grid, stream);
+    }
     if (head_dim == 128) return launch_t<Tile128, P, attn_fwd_kernel<Tile128, P>>(p, grid, stream);
     if (head_dim == 64) return launch_t<Tile64, P, attn_fwd_kernel<Tile64, P>>(p, grid, stream);
   }
