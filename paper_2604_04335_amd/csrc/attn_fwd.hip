@@ -76,15 +76,16 @@ attn_fwd_kernel(const WorkItem* items, P p) {
     const ItemCtx<T> X = begin_item<T, P>(p, items, fresh_lane(), item_idx, row_stride_b);
     const int kv_len = X.it.kv_len, nt = X.nt;
 
-    // Tile ti -> its ring slot.  Only for sequences of two tiles or more, whose tiles are all loaded whole.
-    auto load_k = [&](int ti) {
-      const char* base = X.kbase + (int64_t)tile_first_key<T>(ti, kv_len) * row_stride_b;
+    // Tile ti, which starts at base, -> its ring slot.  Only for sequences of two tiles or more, whose tiles are all loaded
+    // whole, the last one as the last BN keys.
+    const int64_t last_b = (int64_t)(kv_len - T::BN) * row_stride_b;
+    const char *const klast = X.kbase + last_b, *const vlast = X.vbase + last_b;
+    auto load_k = [&](int ti, const char* base) {
       const uint32_t dst = lds_wave + T::K_OFF + (uint32_t)(ti & (NB - 1)) * T::TILE_B;
 #pragma unroll
       for (int i = 0; i < T::LPT; ++i) lds_dma_16(base, kvoff[i], dst + i * T::NWAVES * 1024);
     };
-    auto load_v = [&](int ti) {
-      const char* base = X.vbase + (int64_t)tile_first_key<T>(ti, kv_len) * row_stride_b;
+    auto load_v = [&](int ti, const char* base) {
       const uint32_t dst = lds_wave + T::V_OFF + (uint32_t)(ti & (NB - 1)) * T::TILE_B;
 #pragma unroll
       for (int i = 0; i < T::LPT; ++i) lds_dma_16(base, vvoff[i], dst + i * T::NWAVES * 1024);
@@ -123,9 +124,9 @@ attn_fwd_kernel(const WorkItem* items, P p) {
     bf16x8 qf[T::NKS];
     q_rows_read<T>(p, fresh_lane(), spare, qf);
     wg_barrier();
-    if (nt > 1) load_k(1);
-    if (NB > 2 && nt > 2) load_k(2);
-    if (NB > 2 && nt > 1) load_v(1);
+    if (nt > 1) load_k(1, nt == 2 ? klast : X.kbase + tile_stride_b);
+    if (NB > 2 && nt > 2) load_k(2, nt == 3 ? klast : X.kbase + 2 * tile_stride_b);
+    if (NB > 2 && nt > 1) load_v(1, nt == 2 ? vlast : X.vbase + tile_stride_b);
     mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, sa);
     if (nt > 1) mx = tile_max<T>(sa);
     // Step t: S(t) is in sc; leaves S(t+1) in sn.  Every PER_BAR steps there is a barrier, behind which K(t+1) and V(t) (with
@@ -159,8 +160,9 @@ attn_fwd_kernel(const WorkItem* items, P p) {
         if constexpr (BAR) {
 #pragma unroll
           for (int n = 0; n < PER_BAR; ++n) {
-            if (t + PER_BAR + 1 + n < nt) load_k(t + PER_BAR + 1 + n);
-            if (t + PER_BAR + n < nt) load_v(t + PER_BAR + n);
+            const int tk = t + PER_BAR + 1 + n, tv = t + PER_BAR + n;
+            if (tk < nt) load_k(tk, tk == nt - 1 ? klast : kp + n * tile_stride_b);
+            if (tv < nt) load_v(tv, tv == nt - 1 ? vlast : vp + n * tile_stride_b);
           }
         }
       } else if constexpr (BAR && EVERY == 0) {
@@ -175,12 +177,11 @@ attn_fwd_kernel(const WorkItem* items, P p) {
               if constexpr (J % EVERY == EVERY / 2 && J / EVERY < NLOAD) load_i(IC<J / EVERY>{});
             }
           });
-      if constexpr (MAIN) {
-        if constexpr (BAR) {
-          kp += PER_BAR * tile_stride_b;
-          vp += PER_BAR * tile_stride_b;
-        }
-      } else {
+      if constexpr (BAR) {
+        kp += PER_BAR * tile_stride_b;
+        vp += PER_BAR * tile_stride_b;
+      }
+      if constexpr (!MAIN) {
 #pragma unroll
         for (int ks = 0; ks < T::NKS; ++ks) ka[ks] ^= (((t + 1) ^ (t + 2)) & (NB - 1)) * T::TILE_B;
 #pragma unroll
