@@ -106,7 +106,8 @@ int dit_attn_varlen_fwd(dit_attn_ctx* ctx,
  * time, tight serving loops, harnesses that forbid hipMalloc.  The same operation as dit_attn_varlen_fwd, same
  * arguments, same result bit for bit, but the call allocates nothing and copies nothing: the work-list is written by a
  * small kernel on `stream` (the sequence boundaries travel as its argument) into a fixed device array of the library
- * (256 KB + 256 B per GPU, held until the process ends), which also holds the kernels' work counters.
+ * (256 KB + 256 B per GPU, held until the process ends), which also holds the kernels' work counters.  A pack of at most
+ * 16 sequences whose items all start at once uses neither: its boundaries travel with the attention kernel.
  * Limits: n_seqs <= 64 and at most 16384 work items per pack (an item is 256 query rows of one head, 128 for packs that
  * the 128-row kernel runs; the five benchmark configurations need 32 to 4632); beyond them DIT_ATTN_ERR_LIMIT, `out`
  * untouched.  Unless a kernel is forced, a pack that exceeds the limit only in 128-row items runs the ping-pong kernel.  No split-KV, no plan cache, dit_attn_last_launch_clock is not updated.
@@ -197,24 +198,25 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  * image steps are short, video steps long):
  *     DIT_ATTN_KERNEL_AUTO   (-1) chosen per pack from the lengths, n_heads and
  *                                 head_dim (and the number of compute units):
- *                                 the 128-row kernel while its items leave
- *                                 compute units idle (head_dim 128: under 0.45
- *                                 256-row items per compute unit; head_dim 64:
- *                                 at most one 128-row item) and for cross-
- *                                 attention against few keys (320 per item on
- *                                 average; head_dim 64: 129 to 320); the ping-
- *                                 pong kernel where the 256-row items take no
- *                                 longer than the longest of them.  Past that,
- *                                 head_dim 64: the 128-row kernel up to 100
- *                                 tiles of 64 keys per item on average, but
- *                                 not for self-attention whose short, well
- *                                 filled items are two rounds of the ping-pong
- *                                 kernel and more than one of this, or whose
- *                                 long ones just fill four of the former;
- *                                 else the ping-pong kernel unless its second
- *                                 round would be at most 40 % full or
- *                                 (cross-attention) its items have at most
- *                                 seven such tiles on average
+ *                                 the 128-row kernel while every 128-row item
+ *                                 has a compute unit (head_dim 128: and under
+ *                                 half a 256-row item per compute unit) and
+ *                                 for cross-attention against few keys (320
+ *                                 per item on average; head_dim 64: 129 to
+ *                                 320); the ping-pong kernel where the 256-row
+ *                                 items take no longer than the longest of
+ *                                 them.  Past that, head_dim 64: the 128-row
+ *                                 kernel up to 100 and from 128 tiles of 64
+ *                                 keys per item on average, but not for self-
+ *                                 attention whose short, well filled items are
+ *                                 two rounds of the ping-pong kernel and more
+ *                                 than one of this, or whose long ones just
+ *                                 fill four of the former; else the ping-pong
+ *                                 kernel unless its second round would be at
+ *                                 most three sevenths full, a third round of
+ *                                 equal items at most a quarter, or (cross-
+ *                                 attention) its items have at most eleven
+ *                                 tiles on average
  *     DIT_ATTN_KERNEL_128     (0) 128 query rows per tile
  *     DIT_ATTN_KERNEL_PINGPONG(1) 256 rows per tile, two alternating groups
  * The kernels do the same arithmetic in the same order: their results agree

@@ -38,7 +38,7 @@ struct AttnListParams : AttnParams {
 
 // Two kernels share the tile code.
 //   kIndependent128: 4 wavefronts, 128 query rows per item, two (head dimension 64: three) unsynchronised workgroups per
-//                    compute unit.
+//                    compute unit; a wavefront contracts the next tile's scores beside the softmax of this one.
 //   kPingPong256:    8 wavefronts, 256 query rows per item, one workgroup per compute unit whose two wavefront
 //                    groups alternate between the matrix and the vector phase of consecutive tiles.
 enum class AttnKernel : int { kIndependent128 = 0, kPingPong256 = 1 };
