@@ -266,7 +266,9 @@ namespace {
 // The ping-pong kernel is ahead where a chunk count fills one round of its items, also with queries of less than 128 rows a
 // sequence (4 of 128 x 24 against 4096 keys each unsplit 72 / 45 / 47, 77 x 24 against 20506 keys 347 / 50 / 55, 3 of 100 x 24
 // against 4352, D 64, 55 / 25 / 26);  with under 32 key tiles the shorter items of the 128-row kernel are.
-// The partial results and their merge cost about 9 us, a key tile 1 us per item of the ping-pong kernel at head dimension 128
+// (That sweep was made with kernels whose unsplit times have fallen since, 4951 x 3 to 60 us, and whose fp32 partials were
+// stored in pieces: 4951 x 3 in four chunks takes 46.5 us now.)
+// The partial results and their merge cost about 8 us, a key tile 1 us per item of the ping-pong kernel at head dimension 128
 // and less elsewhere.  What a split has to take off every item, unsplit / split in two, at D 128 and D 64:
 //   12 tiles, 128-row kernel    1536 x 10 30.9 / 27.1, 22.4 / 20.2
 //   16 tiles, ping-pong kernel  2048 x 14 41.1 / 42.6, 28.7 / 28.9;  x 16 44.3 / 46.4, 29.4 / 31.0;  x 12 40.2 / 39.8, 28.6 / 27.9

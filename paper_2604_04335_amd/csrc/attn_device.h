@@ -260,8 +260,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // addressed by ka; step q is k-step q / NKB of key block q % NKB, and step 0 of a block starts it from zero).
 // Operand reads run PD MFMAs ahead of their use, through a ring of PD operand registers.
 // va_ and ka_ pass through the empty asm statements below, so they are taken by reference and stay in their registers
-// (working on copies cost one move per address and tile).  Unrolling the tile loop over the buffer parity, with the
-// buffer as an immediate offset of the LDS instructions and no address arithmetic per tile at all, was 3 % slower.
+// (working on copies cost one move per address and tile).
 template <class T, bool DO_PV, int Q0, int Q1, int PD>
 __device__ __forceinline__ void mfma_stream(lds_char* smem, int (&va_)[T::NDB], int (&ka_)[T::NKS],
                                             const uint32_t (&pb)[T::NKB][8], const bf16x8 (&qf)[T::NKS],
