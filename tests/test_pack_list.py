@@ -113,3 +113,42 @@ def test_no_allocation_one_round(head_dim, lens):
         assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
     finally:
         da.dit_attn_destroy(ctx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lens,heads,kernel", [
+    ([1570], 24, "PINGPONG"),                       # the choice at either head dimension too
+    ([1, 700, 0, 64, 410, 130], 7, "PINGPONG"),
+    ([65 + 70 * i for i in range(16)], 3, "PINGPONG"),
+    ([4096], 16, "PINGPONG"),                       # 256 items: one for every compute unit
+    ([4352], 15, "PINGPONG"),                       # 255, 68 key tiles
+    ([1024], 24, "128"),                            # 192 items of 16 key tiles
+    ([1024], 8, "128"),                             # 64
+    ([1570, 3, 64, 1215], 5, "128"),
+])
+def test_no_allocation_one_round_of_either_kernel(head_dim, lens, heads, kernel):
+    """Every form of both kernels that takes its items from the formula gives the bits of the ordinary call."""
+    import numpy as np
+    import torch
+
+    import paper_2604_04335_amd as da
+
+    print(f"no-allocation, {kernel}: D={head_dim} heads={heads} lens={lens}", flush=True)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(len(lens))
+    q, k, v = (torch.randn((int(cu[-1]), heads, head_dim), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(3))
+    stream = torch.cuda.current_stream().cuda_stream
+    ctx = da.dit_attn_create(0)
+    try:
+        da.dit_attn_set_kernel(ctx, getattr(da, "KERNEL_" + kernel))
+        out, again, ref = (torch.full_like(q, float("nan")) for _ in range(3))
+        da.dit_attn_varlen_fwd(ctx, q, k, v, cu, heads, head_dim, -0.1, ref, stream)
+        da.dit_attn_varlen_fwd_noalloc(ctx, q, k, v, cu, heads, head_dim, -0.1, out, stream)
+        da.dit_attn_varlen_fwd_noalloc(ctx, q, k, v, cu, heads, head_dim, -0.1, again, stream)
+        torch.cuda.synchronize()
+        assert da.dit_attn_last_launch_kernel(ctx) == getattr(da, "KERNEL_" + kernel)
+        assert not bool(ref.isnan().any())
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16)) and torch.equal(again.view(torch.int16), ref.view(torch.int16))
+    finally:
+        da.dit_attn_destroy(ctx)
