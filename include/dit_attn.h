@@ -107,12 +107,14 @@ int dit_attn_varlen_fwd(dit_attn_ctx* ctx,
  * arguments, same result bit for bit, but the call allocates nothing and copies nothing: the work-list is written by a
  * small kernel on `stream` (the sequence boundaries travel as its argument) into a fixed device array of the library
  * (256 KB + 256 B per GPU, held until the process ends), which also holds the kernels' work counters.  A pack of at most
- * 16 sequences whose items all start at once uses neither: its boundaries travel with the attention kernel.
+ * 16 sequences whose items all start at once touches no part of that array: its boundaries travel with the attention
+ * kernel.
  * Limits: n_seqs <= 64 and at most 16384 work items per pack (an item is 256 query rows of one head, 128 for packs that
- * the 128-row kernel runs; the five benchmark configurations need 32 to 4632); beyond them DIT_ATTN_ERR_LIMIT, `out`
- * untouched.  Unless a kernel is forced, a pack that exceeds the limit only in 128-row items runs the ping-pong kernel.  No split-KV, no plan cache, dit_attn_last_launch_clock is not updated.
- * Every call on a GPU shares that GPU's array: calls that overlap on one GPU (two streams, contexts or threads) race;
- * calls on one stream are ordered and safe.  Other return codes as dit_attn_varlen_fwd.
+ * the 128-row kernel runs; the five benchmark configurations need 64 to 4632); beyond them DIT_ATTN_ERR_LIMIT, `out`
+ * untouched.  Unless a kernel is forced, a pack that exceeds the limit only in 128-row items runs the ping-pong kernel.
+ * No split-KV, no plan cache, dit_attn_last_launch_clock is not updated.
+ * The other packs on a GPU share that GPU's array: calls with such packs that overlap on one GPU (two streams, contexts or
+ * threads) race; calls on one stream are ordered and safe.  Other return codes as dit_attn_varlen_fwd.
  */
 int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx,
                                 const void* q, const void* k, const void* v,

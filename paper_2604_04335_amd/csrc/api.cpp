@@ -537,10 +537,8 @@ int dit_attn_varlen_fwd_noalloc(dit_attn_ctx* ctx, const void* q, const void* k,
   hipStream_t s = static_cast<hipStream_t>(stream);
   dit::AttnParams p{};
   dit::PackList list;
-  if (n_items <= static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel, head_dim) &&
-      dit::pack_list_build(cu_seqlens, cu_seqlens, n_seqs, n_heads, bm, list)) {
-    p.sync = dit::noalloc_sync(ctx->device);
-  } else {
+  if (n_items > static_cast<int64_t>(ctx->n_cus) * dit::attn_fwd_wgs_per_cu(kernel, head_dim) ||
+      !dit::pack_list_build(cu_seqlens, cu_seqlens, n_seqs, n_heads, bm, list)) {
     e = dit::noalloc_plan_launch(ctx->device, cu_seqlens, n_seqs, n_heads, bm, static_cast<uint32_t>(n_items), s, &p.items, &p.sync);
     if (e != hipSuccess) return fail_hip(ctx, e, "work-list kernel launch");
   }

@@ -703,11 +703,12 @@ __device__ __forceinline__ uint32_t take_item(const AttnParams& p) {
 
 // Clock sample of a launch: workgroup 0 (persistent, so it lives about as long as the kernel) reads the shader-cycle
 // counter and the constant 100 MHz counter when it starts and when it ends, and leaves the two differences in
-// sync[2..5].  Their ratio is the shader clock the chip sustained under this kernel.
+// sync[2..5].  Their ratio is the shader clock the chip sustained under this kernel.  A launch whose items are a formula takes
+// none: nobody reads it there, and such a launch shares no memory with any other.
 struct LaunchClock {
   uint64_t cycles, ticks;
 };
-__device__ __forceinline__ LaunchClock launch_clock_begin() {
+__device__ __forceinline__ LaunchClock launch_clock_begin(const AttnParams&) {
   LaunchClock c;
   c.cycles = __builtin_readcyclecounter();
   c.ticks = __builtin_amdgcn_s_memrealtime();
@@ -720,6 +721,8 @@ __device__ __forceinline__ void launch_clock_end(const AttnParams& p, const Laun
     out[1] = __builtin_amdgcn_s_memrealtime() - c0.ticks;
   }
 }
+__device__ __forceinline__ LaunchClock launch_clock_begin(const AttnListParams&) { return {}; }
+__device__ __forceinline__ void launch_clock_end(const AttnListParams&, const LaunchClock&) {}
 
 // Work item fields, wave-uniform.
 struct ItemU {

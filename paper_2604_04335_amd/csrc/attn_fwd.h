@@ -29,7 +29,7 @@ struct AttnParams {
   int32_t negate;           // 1 when scale < 0: the sign of Q is flipped on load
 };
 
-// The parameters of a launch with no more items than workgroups whose items are a formula (items is not read).  A type and
+// The parameters of a launch with no more items than workgroups whose items are a formula (items and sync are not read).  A type and
 // kernel instances of their own: with the list among the arguments of every launch the small packs of the ordinary entry
 // points took 0.25 us longer (410 rows x 24 heads at head dimension 64, 7.8 -> 8.05).
 struct AttnListParams : AttnParams {

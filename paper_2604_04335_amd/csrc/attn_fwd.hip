@@ -40,7 +40,7 @@ attn_fwd_kernel(const WorkItem* items, P p) {
   lds_slot* s_item = reinterpret_cast<lds_slot*>(smem + T::ITEM_OFF);
 
   constexpr int NB = T::NBUF;
-  const LaunchClock clock0 = launch_clock_begin();
+  const LaunchClock clock0 = launch_clock_begin(p);
   const int tid = threadIdx.x;
   const int64_t row_stride_b = (int64_t)p.n_heads * T::D * 2;
   const float c = p.c_log2;
@@ -269,7 +269,7 @@ attn_fwd_pp_kernel(const WorkItem* items, P p) {
   lds_char* smem = (lds_char*)smem_generic;
   lds_slot* s_item = reinterpret_cast<lds_slot*>(smem + T::ITEM_OFF);
 
-  const LaunchClock clock0 = launch_clock_begin();
+  const LaunchClock clock0 = launch_clock_begin(p);
   const int tid = threadIdx.x;
   const int64_t row_stride_b = (int64_t)p.n_heads * T::D * 2;
   const float c = p.c_log2;

@@ -14,9 +14,6 @@ constexpr int32_t kNoAllocMaxItems = 16384;   // work items per pack: 256 KB of 
 // the scratch array, clears the work counters and loads the plan kernel.  Repeated calls are no-ops.
 hipError_t noalloc_init(int device);
 
-// The device address of the scratch's sync words, for a launch that needs no list (PackList); nullptr before noalloc_init.
-uint32_t* noalloc_sync(int device);
-
 // Enqueues on `stream` the kernel that writes the work-list of this pack (block_m query rows per item; n_items as
 // counted by the caller) into the device's scratch and clears the work counters there; returns the device addresses of
 // the list and of the sync words for the attention launch that follows on the same stream.  Allocates nothing.

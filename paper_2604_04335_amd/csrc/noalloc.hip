@@ -8,6 +8,10 @@
 // start at once needs neither list nor counters: its sequences travel with the attention kernel itself (PackList) and this
 // kernel falls away.  us a call with it / without: 410 rows x 24 heads at head dimension 64 11.5 / 8.1, eight sequences of
 // 256 rows x 8 11.4 / 6.9, 1570 x 24 at 128 40.5 / 37.2.
+//
+// Every call that does need them shares its GPU's copy of the array: such calls that overlap on one GPU (two streams, two
+// contexts, two threads) race.  The array keeps the last call's contents; the plan kernel rewrites every item that the next
+// launch reads and clears the work counter, so nothing is assumed about what an earlier call left.
 #include "noalloc.h"
 
 namespace dit {
@@ -88,10 +92,6 @@ hipError_t noalloc_init(int device) {
   if (e != hipSuccess) return e;
   g_scratch_ptr[device] = ptr;
   return hipSuccess;
-}
-
-uint32_t* noalloc_sync(int device) {
-  return device >= 0 && device < kMaxDevices ? reinterpret_cast<uint32_t*>(g_scratch_ptr[device]) : nullptr;
 }
 
 hipError_t noalloc_plan_launch(int device, const int32_t* cu_seqlens, int32_t n_seqs, int32_t n_heads, int32_t block_m,

@@ -1,6 +1,10 @@
-"""What the compiler's metadata in the built library says of every kernel: no private segment (a kernel with one has the
-runtime provide scratch memory on its queue, also at the entry point that allocates nothing) and no spilled vector register."""
+"""What the built library says of its kernels.  Its metadata: no private segment (a kernel with one has the runtime provide
+scratch memory on its queue, also at the entry point that allocates nothing) and no spilled vector register.  Its
+instructions: what a launch may share with others."""
+import os
+import re
 import struct
+import subprocess
 
 import pytest
 
@@ -8,6 +12,7 @@ from paper_2604_04335_amd.build import LIB_PATH
 
 msgpack = pytest.importorskip("msgpack")
 
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 NOTE = struct.pack("<I", 32) + b"AMDGPU\0\0"  # an ELF note's type (code object metadata) and name; its sizes stand before
 
 
@@ -27,3 +32,32 @@ def test_no_kernel_uses_scratch():
     for part in ("attn_fwd_kernel", "attn_fwd_pp_kernel", "AttnListParams", "noalloc_plan_kernel", "merge_kernel", "sp_"):
         assert any(part in n for n in kernels), part
     assert not {n: v for n, v in kernels.items() if v != (0, 0)}
+
+
+def _listing(tmp_path):
+    """{kernel name: its instructions} of the code object that holds the attention kernels."""
+    blob = open(LIB_PATH, "rb").read()
+    starts = [m.start() for m in re.finditer(re.escape(b"\x7fELF"), blob)][1:]  # the first is the host library's own
+    for i, at in enumerate(starts):
+        part = blob[at:starts[i + 1] if i + 1 < len(starts) else len(blob)]
+        if b"attn_fwd_pp_kernel" in part and NOTE in part:
+            (tmp_path / "code").write_bytes(part)
+            break
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(tmp_path / "code")], capture_output=True, text=True, check=True).stdout
+    kernels, lines = {}, None
+    for line in text.splitlines():
+        head = re.match(r"^[0-9a-f]+ <(\w+)>:$", line)
+        if head:
+            lines = kernels.setdefault(head.group(1), [])
+        elif lines is not None and line.strip():
+            lines.append(line.split("//")[0].strip())
+    return {n: v for n, v in kernels.items() if "attn_fwd" in n}
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_launches_by_formula_share_no_memory(tmp_path):
+    """A pack whose items travel with the kernel takes no work counter and leaves no clock sample: nothing that calls on other
+    streams could share."""
+    for name, lines in _listing(tmp_path).items():
+        shares = [x for x in lines if x.startswith(("global_atomic", "s_memtime", "s_memrealtime"))]
+        assert (len(shares) == 0) == ("AttnListParams" in name), (name, shares)
