@@ -439,6 +439,15 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // How far (in the base-2 exponent) a tile's row maximum may exceed the row's reference value before the reference moves.
 constexpr float kRescaleLog2 = 8.0f;
 
+// Between the last MFMA of a tile's scores and tile_max right behind it.  A vector instruction may read the result of an
+// MFMA of 8 passes 12 wait states after it at the earliest; the compiler keeps that distance for its own instructions but
+// counts none in front of inline asm.  (Elsewhere a barrier and address arithmetic, or other MFMAs, stand in between.)
+template <class T>
+__device__ __forceinline__ void scores_ready(f32x16 (&s)[T::NKB]) {
+  static_assert(T::NKB == 2, "two key blocks per tile");
+  asm volatile("s_nop 11" : "+v"(s[0]), "+v"(s[1]));
+}
+
 // Maximum over a tile's scores for this lane's query row (both halves of the wavefront).
 template <class T>
 __device__ __forceinline__ float tile_max(const f32x16 (&s)[T::NKB]) {

@@ -128,6 +128,7 @@ attn_fwd_kernel(const WorkItem* items, P p) {
     if (NB > 2 && nt > 2) load_k(2, nt == 3 ? klast : X.kbase + 2 * tile_stride_b);
     if (NB > 2 && nt > 1) load_v(1, nt == 2 ? vlast : X.vbase + tile_stride_b);
     mfma_stream<T, false, 0, T::NQK, kPrefetch>(smem, va, ka, pb, qf, o, sa);
+    scores_ready<T>(sa);
     if (nt > 1) mx = tile_max<T>(sa);
     // Step t: S(t) is in sc; leaves S(t+1) in sn.  Every PER_BAR steps there is a barrier, behind which K(t+1) and V(t) (with
     // two steps to a barrier also K(t+2) and V(t+1)) have landed for everyone and nobody reads the tiles before them any

@@ -1,6 +1,6 @@
 """What the built library says of its kernels.  Its metadata: no private segment (a kernel with one has the runtime provide
 scratch memory on its queue, also at the entry point that allocates nothing) and no spilled vector register.  Its
-instructions: what a launch may share with others."""
+instructions: what a launch may share with others, and how far a matrix instruction is from the first reader of its result."""
 import os
 import re
 import struct
@@ -61,3 +61,32 @@ def test_launches_by_formula_share_no_memory(tmp_path):
     for name, lines in _listing(tmp_path).items():
         shares = [x for x in lines if x.startswith(("global_atomic", "s_memtime", "s_memrealtime"))]
         assert (len(shares) == 0) == ("AttnListParams" in name), (name, shares)
+
+
+def _registers(operand):
+    m = re.match(r"^v\[?(\d+)(?::(\d+))?\]?$", operand.strip())
+    return set(range(int(m.group(1)), int(m.group(2) or m.group(1)) + 1)) if m else set()
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_maxima_wait_for_their_scores(tmp_path):
+    """The row maxima are inline asm, in front of which the compiler inserts no wait states.  12 of them must lie between an MFMA
+    of 8 passes and a reader of its result: one per instruction, n + 1 for s_nop n; the next MFMA issues 8 after the last."""
+    checked = 0
+    for name, lines in _listing(tmp_path).items():
+        for i, line in enumerate(lines):
+            if not line.startswith("v_mfma"):
+                continue
+            result = _registers(line.split(None, 1)[1].split(",")[0])
+            now, last = 1, 0  # in wait states since the MFMA issued
+            for after in lines[i + 1:]:
+                op, _, operands = after.partition(" ")
+                if now > 12 or op in ("s_branch", "s_endpgm"):
+                    break
+                if op == "v_max3_f32":
+                    checked += 1
+                    assert not result & set().union(*(_registers(x) for x in operands.split(",")[1:])), (name, line, after, now - 1)
+                if op.startswith("v_mfma"):
+                    now = last = max(now, last + 8)
+                now += int(operands) + 1 if op == "s_nop" else 1
+    assert checked > 0
