@@ -33,7 +33,10 @@ void plan_build_cross(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, 
     if (cu_k[i + 1] > cu_k[i])
       total += static_cast<size_t>((len + block_m - 1) / block_m) * static_cast<size_t>(n_heads) * static_cast<size_t>(n_splits);
   }
-  items.reserve(total);
+  // Written through a pointer into a list of full size: a new pack's first call waits for this.  46618 x 24 rows against 512
+  // keys, 8760 records, us: 24;  pushed back one by one, with the loop over chunks for every tile, 90.
+  items.resize(total);  // an upper bound: a sequence may have fewer chunks than n_splits
+  WorkItem* out = items.data();
   for (int32_t s : order) {
     const int32_t q0 = cu_q[s], q_len = cu_q[s + 1] - cu_q[s];
     const int32_t k0 = cu_k[s], k_len = cu_k[s + 1] - cu_k[s];
@@ -41,20 +44,25 @@ void plan_build_cross(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, 
     const int32_t tiles = (k_len + block_n - 1) / block_n;
     const int32_t tiles_per_part = (tiles + n_splits - 1) / n_splits;
     const int32_t chunk = tiles_per_part * block_n;
-    auto push_tile = [&](int32_t h, int32_t m0) {
-      const int32_t rows = std::min(block_m, q_len - m0);
+    auto put_tile = [&](int32_t m0, int32_t rows, int32_t h) {
+      const int32_t rows_head = (rows << 16) | h;
+      if (k_len <= chunk) {
+        *out++ = WorkItem{q0 + m0, k0, k_len, rows_head};
+        return;
+      }
       for (int32_t part = 0, kb = 0; kb < k_len; ++part, kb += chunk)
-        items.push_back(WorkItem{q0 + m0, k0 + kb, std::min(chunk, k_len - kb), (part << 28) | (rows << 16) | h});
+        *out++ = WorkItem{q0 + m0, k0 + kb, std::min(chunk, k_len - kb), (part << 28) | rows_head};
     };
     // Whole query tiles of all heads first, then the ragged last tile of every head: a ragged tile is quicker (its
     // wavefronts without rows compute nothing), and a workgroup that gets ahead of the others in the middle of a
     // sequence streams K and V on its own from then on instead of sharing them in L2 with the workgroups beside it.
     const int32_t whole = q_len / block_m * block_m;
     for (int32_t h = 0; h < n_heads; ++h)
-      for (int32_t m0 = 0; m0 < whole; m0 += block_m) push_tile(h, m0);
+      for (int32_t m0 = 0; m0 < whole; m0 += block_m) put_tile(m0, block_m, h);
     if (whole < q_len)
-      for (int32_t h = 0; h < n_heads; ++h) push_tile(h, whole);
+      for (int32_t h = 0; h < n_heads; ++h) put_tile(whole, q_len - whole, h);
   }
+  items.resize(static_cast<size_t>(out - items.data()));
 }
 
 bool pack_list_build(const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads, int32_t block_m, PackList& list) {

@@ -68,15 +68,69 @@ int main() {
 """
 
 
-def test_formula_equals_list(tmp_path):
+LIST_PROGRAM = r"""
+#include "plan.h"
+#include <algorithm>
+#include <cstdio>
+#include <cstring>
+#include <random>
+using namespace dit;
+int main() {
+  std::mt19937 rng(11);
+  auto pick = [&](int lo, int hi) { return lo + static_cast<int>(rng() % static_cast<unsigned>(hi - lo + 1)); };
+  std::vector<WorkItem> items;
+  for (int trial = 0; trial < 20000; ++trial) {
+    const int n = pick(0, 12), heads = pick(1, 30), splits = pick(0, 1) ? 1 : pick(2, 15), bm = pick(0, 1) ? 128 : 256;
+    std::vector<int32_t> cq(1, 0), ck(1, 0);
+    for (int i = 0; i < n; ++i) {
+      cq.push_back(cq.back() + pick(0, 3) * pick(0, 400));
+      ck.push_back(ck.back() + pick(0, 3) * pick(0, 1500));
+    }
+    // as the list is defined: most keys first, heads, whole query tiles, the ragged tiles behind them, chunks of whole key tiles
+    std::vector<int> order;
+    for (int i = 0; i < n; ++i) order.push_back(i);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return ck[a + 1] - ck[a] > ck[b + 1] - ck[b]; });
+    std::vector<WorkItem> want;
+    for (int s : order)
+      for (int ragged = 0; ragged < 2; ++ragged)
+        for (int h = 0; h < heads; ++h)
+          for (int m = cq[s]; m < cq[s + 1]; m += bm) {
+            const int rows = std::min(bm, cq[s + 1] - m), keys = ck[s + 1] - ck[s], chunk = ((keys + 63) / 64 + splits - 1) / splits * 64;
+            if ((rows < bm) != (ragged == 1)) continue;
+            for (int part = 0; part * chunk < keys; ++part)
+              want.push_back(WorkItem{m, ck[s] + part * chunk, std::min(chunk, keys - part * chunk), (part << 28) | (rows << 16) | h});
+          }
+    if (trial % 3 == 0) items.assign(7, WorkItem{1, 2, 3, 4});  // what an earlier call left does not matter
+    plan_build_cross(cq.data(), ck.data(), n, heads, bm, items, splits);
+    if (items.size() != want.size() || (!want.empty() && std::memcmp(items.data(), want.data(), want.size() * sizeof(WorkItem)) != 0)) {
+      std::printf("trial %d: %zu records, expected %zu\n", trial, items.size(), want.size());
+      return 1;
+    }
+  }
+  return 0;
+}
+"""
+
+
+def _run(program, tmp_path):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no host compiler")
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, str(src), os.path.join(CSRC, "plan.cpp"), "-o", str(exe)], check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout
+
+
+def test_formula_equals_list(tmp_path):
+    _run(PROGRAM, tmp_path)
+
+
+def test_list_as_defined(tmp_path):
+    """plan_build_cross, record for record, against a plain statement of its order: any number of chunks, empty sequences on
+    either side, a list object used before."""
+    _run(LIST_PROGRAM, tmp_path)
 
 
 @pytest.mark.gpu
