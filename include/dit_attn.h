@@ -201,9 +201,8 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  *     DIT_ATTN_KERNEL_AUTO   (-1) chosen per pack from the lengths, n_heads and
  *                                 head_dim (and the number of compute units):
  *                                 the 128-row kernel while every 128-row item
- *                                 has a compute unit (head_dim 128: and under
- *                                 half a 256-row item per compute unit) and
- *                                 for cross-attention against few keys (320
+ *                                 has a compute unit and for cross-attention
+ *                                 against few keys (320
  *                                 per item on average; head_dim 64: 129 to
  *                                 320); the ping-pong kernel where the 256-row
  *                                 items take no longer than the longest of

@@ -567,11 +567,11 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
     tiles += it * nt;
     max_tiles = nt > max_tiles ? nt : max_tiles;
   }
-  // Every 128-row item has a compute unit of its own: nothing is gained by longer ones.  D 128: 1280 x 24 27.5 / 30.9,
-  // 1536 x 21 31.6 / 35.5, 2048 x 15 34.4 / 44.0;  past it 1300 x 24 36.7 / 32.3, 1408 x 24 38.2 / 33.2.  (So are 128 items of 256 rows
-  // that are all whole, 4096 x 8 66 / 88, whose block_m of dit_attn_plan is what callers know, and stays.)  D 64: 1280 x 24
-  // 17.1 / 23.4, 410 x 24 7.8 / 11.7;  past it 1281 x 24 24.1 / 24.7.
-  if (items128 <= n_cus && (head_dim == 64 || 2 * items256 < n_cus)) return AttnKernel::kIndependent128;
+  // Every 128-row item has a compute unit of its own: nothing is gained by longer ones.  D 128: 1280 x 24 25.7 / 30.9,
+  // 2048 x 15 34.8 / 44.0, 2100 x 15 37.5 / 45.0, 4096 x 8 65.3 / 80, 1300 x 23 27.6 / 31.7, 16 of 200 x 8 8.4 / 11.8;  past it
+  // 1300 x 24 35.8 / 32.1, 1408 x 24 37.1 / 32.5, 2048 x 17 50.3 / 44.3, 4096 x 9 94 / 81.  D 64: 1280 x 24 17.1 / 23.4, 410 x 24
+  // 7.8 / 11.7;  past it 1300 x 24 23.4 / 24.6, 1792 x 24 30.6 / 30.4, 8192 x 6 121 / 120.
+  if (items128 <= n_cus) return AttnKernel::kIndependent128;
   // Items with few key tiles (cross-attention against text keys): the 128-row kernel's workgroups have no idle phase at
   // the ends of an item.  46618 x 24, D 128: 77 keys 149 / 178, 226: 202 / 224, 512: 322 / 334, 640: 379 / 386 (8704 x 24: 73 /
   // 79), 768: 438 / 439;  D 64: 200 keys 112 / 148.  At D 64 one or two tiles are bound by Q and O, which the larger items move

@@ -62,10 +62,13 @@ def test_cross_choice_at_head_dim_64(n_keys, kernel):
 
 
 @pytest.mark.parametrize("lens,heads,head_dim,block_m", [
-    ([1280], 24, 128, 128),          # 240 items of 128 rows, 120 of 256: under half of the compute units
+    ([1280], 24, 128, 128),          # 240 items of 128 rows: each has a compute unit of its own
     ([1281], 24, 128, 256),          # 264 items of 128 rows
     ([2048], 15, 128, 128),
-    ([2048], 16, 128, 256),          # 128 items of 256 rows
+    ([2048], 16, 128, 128),          # 256 of them, each with a compute unit of its own: 36 us, the ping-pong kernel 44
+    ([2048], 17, 128, 256),
+    ([2100], 15, 128, 128),          # 255, although 135 items of 256 rows are more than half of the compute units
+    ([200] * 16, 8, 128, 128),       # 256 ragged ones
     ([3600], 24, 128, 128),          # 360: a second round 41 % full
     ([3841], 23, 128, 256),          # 368: 44 %
     ([6000], 24, 128, 128),          # 576 equal items: a third round a quarter full
