@@ -202,22 +202,19 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  *                                 head_dim (and the number of compute units):
  *                                 the 128-row kernel while every 128-row item
  *                                 has a compute unit and for cross-attention
- *                                 against few keys (320
- *                                 per item on average; head_dim 64: 129 to
- *                                 320); the ping-pong kernel where the 256-row
- *                                 items take no longer than the longest of
- *                                 them.  Past that, head_dim 64: the 128-row
- *                                 kernel up to 100 and from 128 tiles of 64
- *                                 keys per item on average, but not for self-
- *                                 attention whose short, well filled items are
- *                                 two rounds of the ping-pong kernel and more
- *                                 than one of this, or whose long ones just
- *                                 fill four of the former; else the ping-pong
- *                                 kernel unless its second round would be at
- *                                 most three sevenths full, a third round of
- *                                 equal items at most a quarter, or (cross-
- *                                 attention) its items have at most eleven
- *                                 tiles on average
+ *                                 against few keys (320 per item on average;
+ *                                 head_dim 64: 129 to 320); the ping-pong
+ *                                 kernel where the 256-row items take no
+ *                                 longer than the longest of them.  Past that,
+ *                                 head_dim 64: the 128-row kernel, but not for
+ *                                 self-attention whose short, well filled
+ *                                 items are two rounds of the ping-pong kernel
+ *                                 and more than one of this; head_dim 128: the
+ *                                 ping-pong kernel unless its second round
+ *                                 would be at most three sevenths full, a third
+ *                                 round of equal items at most a quarter, or
+ *                                 (cross-attention) its items have at most
+ *                                 eleven tiles of 64 keys on average
  *     DIT_ATTN_KERNEL_128     (0) 128 query rows per tile
  *     DIT_ATTN_KERNEL_PINGPONG(1) 256 rows per tile, two alternating groups
  * The kernels do the same arithmetic in the same order: their results agree

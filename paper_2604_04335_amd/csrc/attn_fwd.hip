@@ -582,31 +582,27 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
   // 1570 x 24 43.5 / 37.3, 410 and 2458 x 24 78.4 / 71.7, against 512 keys 19.6 / 18.3;  D 64: 1570 x 24 28.1 / 28.3, 2458 x 24
   // 45.2 / 44.3.
   if (tiles <= n_cus * max_tiles) return AttnKernel::kPingPong256;
-  // Past one round at D 64 three workgroups of the 128-row kernel share a compute unit and are ahead in general: 512 x 24
-  // heads x 18 sequences 45.0 / 48.1, 1024 x 24 x 9 70.3 / 79.4, 1536 x 24 x 6 93 / 112, 3000 x 24 73 / 98, 3600 x 24 93 / 122,
-  // 4352 x 24 135 / 145, 2049 x 24 x 6 176 / 198, 6000 x 24 233 / 287, 4352 x 24 x 4 451 / 509, 46618 x 24 against 512 keys 172 /
-  // 215.  Batches of several lengths too: 3167, 537, 876 and 322 rows 85 / 104, 4 each of 4352, 2458, 1054 and 410 635 / 700,
-  // 410 to 4250 rows 325 / 350, 421 to 3916 rows x 12 86 / 89.
-  // The exceptions, for self-attention:
-  if (head_dim == 64 && cu_seqlens_k == nullptr) {
-    // Short items that are two rounds for the ping-pong kernel and more than one for the 128-row kernel, whose second round
-    // costs more than its share (a workgroup alone on its compute unit takes some 0.6 of what three take together):
-    // 410 x 24 x 9 24.7 / 24.4, 745 x 24 x 7 35.9 / 35.7, 925 x 12 x 10 42.4 / 39.7, 1054 x 24 x 4 44.8 / 42.6, 512 x 24 x 9
-    // 30.1 / 26.3, 1024 x 24 x 5 47.2 / 42.4.  Not where the 256-row items hold under 200 rows on average: 520 x 24 x 7 27.7 /
-    // 28.7, 588 x 24 x 7 29.8 / 30.4 (790 x 24 x 5 36.1 / 35.6);  not with a third round: 1120 x 24 x 5 51.9 / 59.8, 1331 x 12
-    // x 8 57 / 67, 1024 x 24 x 6 54.0 / 58.2 (three full ones: 512 x 24 x 16 42.8 / 39.4, 1024 x 24 x 8 66.3 / 65.5);  not with
-    // one round: 300 x 24 x 10 14.8 / 20.4.  The 128-row kernel has come to be ahead between 18 and 24 tiles (1300 x 12 x 6 46.2 /
-    // 49.5, 1536 x 24 x 3 54.0 / 57.6) and in the rule below by 2 to 8 % (2458 x 24 x 4 162 / 172, 3750 x 8 x 8 240 / 258, 5120 x
-    // 24 x 2 331 / 341, 3000 x 12 x 7 208 / 212), as at 101 to 127 tiles further down (7000 x 24 327 / 339): block_m of
-    // dit_attn_plan for such packs is what callers know, and stays.
-    if (tiles <= 24 * items256 && items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus && rows >= 200 * items256)
-      return AttnKernel::kPingPong256;
-    // Longer items that just fill a fourth round of the ping-pong kernel leave the 128-row kernel a third one half full.
-    if (tiles > 24 * items256 && 4 * items256 >= 15 * (int64_t)n_cus && items256 <= 4 * (int64_t)n_cus) return AttnKernel::kPingPong256;
+  // Past one round at D 64 three workgroups of the 128-row kernel share a compute unit and are ahead: 512 x 24 heads x 18
+  // sequences 45.4 / 51.6, 768 x 24 x 8 42.9 / 51.1, 1536 x 24 x 6 93 / 112, 3000 x 24 73 / 98, 4352 x 24 132 / 145, 6000 x 24 233 /
+  // 287, 2458 x 24 x 4 164 / 174, 3000 x 12 x 7 203 / 213, 5120 x 24 x 2 331 / 336, 4352 x 24 x 4 451 / 509, 7000 x 24 318 / 337,
+  // 8128 x 24 395 / 416, 9000 x 24 490 / 560, 20506 x 24 2450 / 2560, 46618 x 24 against 512 keys 172 / 205;  level at 1024 x 24 x
+  // 8 (68.1 / 67.6), 512 x 24 x 16 (41.6 / 41.8), 10000 x 24 (639 / 641), 16384 x 16 (1078 / 1083) and 13000 x 10 x 2 (859 / 857).
+  // Batches of several lengths: 3167, 537, 876 and 322 rows 85 / 104, 4 each of 4352, 2458, 1054 and 410 635 / 700, 410 to 4250
+  // rows 325 / 350, 421 to 3916 rows x 12 86 / 89, 8192, 300 and 77 x 12 211 / 276.
+  if (head_dim == 64) {
+    // The exception: short items of self-attention that are two rounds for the ping-pong kernel and more than one for the
+    // 128-row kernel, whose second round costs more than its share (a workgroup alone on its compute unit takes some 0.6 of
+    // what three take together).  Its times scatter there, from card to card and with the rows: whole tiles 512 x 24 x 9 27.8 to
+    // 30.2 / 26.5 to 28.6, 640 x 24 x 7 32.4 to 34.7 / 30.3 to 31.5, 768 x 8 x 20 38 to 42 / 35.6 to 38.4, 1024 x 24 x 5 47.2 to
+    // 48.7 / 43.3 to 45.9, 1024 x 8 x 16 48.0 to 49.9 / 44.5 to 47.6;  ragged ones 410 x 24 x 9 23.5 to 28.9 / 24.4 to 26.2, 745 x 24
+    // x 7 35.7 to 38.7 / 37.6 to 39.9, 925 x 12 x 10 40.9 to 42.8 / 39.7 to 44.1, 1054 x 24 x 4 43.7 to 45.2 / 42.6 to 47.3.  Up to 17
+    // key tiles: 1152 x 24 x 4 45.5 / 45.5, 1200 x 24 x 4 49.4 / 49.9 to 52.9, 1280 x 24 x 4 51.3 / 52.4 to 55.2, 1536 x 24 x 3 55.0 /
+    // 57.1 to 61.6.  Not where the 256-row items hold under 200 rows on average: 520 x 24 x 7 27.7 / 28.7, 588 x 24 x 7 29.8 / 30.4;
+    // not with a third round: 1120 x 24 x 5 51.9 / 59.8, 1152 x 24 x 5 54.4 / 64.1;  not with one round: 300 x 24 x 10 14.8 / 20.4.
+    const bool two_rounds = items128 > 3 * (int64_t)n_cus && items256 <= 2 * (int64_t)n_cus;
+    if (cu_seqlens_k == nullptr && two_rounds && tiles <= 17 * items256 && rows >= 200 * items256) return AttnKernel::kPingPong256;
+    return AttnKernel::kIndependent128;
   }
-  // Longer packs: 8192 x 24 407 / 416, 9000 x 24 487 / 580, 12000 x 24 861 / 954, 16000 x 24 1556 / 1536, 20506 x 24 2483 / 2599,
-  // 8192, 300 and 77 x 12 211 / 276.
-  if (head_dim == 64 && (tiles <= 100 * items256 || tiles >= 128 * items256)) return AttnKernel::kIndependent128;
   // Else the ping-pong kernel (D 128: 7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
   // up to eleven key tiles (see above) and equal items that leave much of its last round empty: a second round at most three
   // sevenths full (2600 x 24 84 / 102, 3200 x 24 133 / 142, 3600 x 24 159 / 172, 1500 x 20 x 3 78.5 / 86;  half full, 4000 x 24

@@ -13,7 +13,7 @@ import paper_2604_04335_amd as da
     ([2049] * 6, 24, 64, 128),       # 33 key tiles
     ([4352] * 4, 24, 64, 128),
     ([6400], 24, 64, 128),           # 100 key tiles
-    ([6401], 24, 64, 256),           # 101
+    ([6401], 24, 64, 128),           # 101: 283 us, the ping-pong kernel 298
     ([1054] * 4, 24, 64, 256),       # 864 items of 128 rows: a second round of 96 of them
     ([300] * 10, 24, 64, 128),       # 720: one round
     ([410] * 8 + [250], 24, 64, 256),      # 816, 408 items of 256 rows
@@ -21,11 +21,13 @@ import paper_2604_04335_amd as da
     ([399] * 9, 24, 64, 128),
     ([1024] * 16, 8, 64, 256),       # 1024 items of 128 rows, 512 of 256: two full rounds
     ([1024] * 16 + [30], 8, 64, 128),      # 520: a third round
-    ([1536] * 3, 24, 64, 256),       # 24 key tiles, 864 items of 128 rows
+    ([1088] * 4, 24, 64, 256),       # 17 key tiles, 864 items of 128 rows
+    ([1089] * 4, 24, 64, 128),       # 18
+    ([1536] * 3, 24, 64, 128),       # 24: 55 us, the ping-pong kernel 57
     ([1537] * 3, 24, 64, 128),       # 25
-    ([2458] * 4, 24, 64, 256),       # 960 items of 256 rows: a fourth round three quarters full
+    ([2458] * 4, 24, 64, 128),       # 960 items of 256 rows, a fourth round three quarters full: 164 us, 174
     ([2458] * 3 + [2304], 24, 64, 128),    # 936
-    ([4096] * 8, 8, 64, 256),        # 1024: four full rounds
+    ([4096] * 8, 8, 64, 128),        # 1024, four full rounds: 278 us, 284
     ([4096] * 8 + [30], 8, 64, 128),       # 1032
     ([4250, 410], 13, 64, 256),      # 247 items, one round
     ([2458, 410], 24, 128, 256),     # 288 items whose second round is made of short ones: no longer than the longest item
@@ -74,7 +76,7 @@ def test_cross_choice_at_head_dim_64(n_keys, kernel):
     ([6000], 24, 128, 128),          # 576 equal items: a third round a quarter full
     ([6000], 25, 128, 256),          # 600
     ([6000, 3000], 17, 128, 256),    # 612 items of two lengths: the short ones fill the round
-    ([8128], 24, 64, 256),           # 127 key tiles
+    ([8128], 24, 64, 128),           # 127 key tiles: 395 us, the ping-pong kernel 416
     ([8129], 24, 64, 128),           # 128
 ])
 def test_kernel_choice_of_fuller_rounds(lens, heads, head_dim, block_m):
