@@ -210,11 +210,13 @@ int dit_attn_sp_unpack_heads(dit_attn_ctx* ctx, const void* src, void* dst, int6
  *                                 self-attention whose short, well filled
  *                                 items are two rounds of the ping-pong kernel
  *                                 and more than one of this; head_dim 128: the
- *                                 ping-pong kernel unless its second round
- *                                 would be at most three sevenths full, a third
- *                                 round of equal items at most a quarter, or
+ *                                 ping-pong kernel unless its second round, or
+ *                                 a third one of equal items, would be at most
+ *                                 half full (a second one of self-attention
+ *                                 with up to eleven tiles of 64 keys per item
+ *                                 three sevenths, and not with 12 to 18), or
  *                                 (cross-attention) its items have at most
- *                                 eleven tiles of 64 keys on average
+ *                                 eleven tiles on average
  *     DIT_ATTN_KERNEL_128     (0) 128 query rows per tile
  *     DIT_ATTN_KERNEL_PINGPONG(1) 256 rows per tile, two alternating groups
  * The kernels do the same arithmetic in the same order: their results agree

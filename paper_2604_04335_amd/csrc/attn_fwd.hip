@@ -603,17 +603,32 @@ AttnKernel attn_fwd_select(const int32_t* cu_seqlens, const int32_t* cu_seqlens_
     if (cu_seqlens_k == nullptr && two_rounds && tiles <= 17 * items256 && rows >= 200 * items256) return AttnKernel::kPingPong256;
     return AttnKernel::kIndependent128;
   }
-  // Else the ping-pong kernel (D 128: 7 to 18 % ahead from 1.75 items per compute unit on), but for cross-attention items of
-  // up to eleven key tiles (see above) and equal items that leave much of its last round empty: a second round at most three
-  // sevenths full (2600 x 24 84 / 102, 3200 x 24 133 / 142, 3600 x 24 159 / 172, 1500 x 20 x 3 78.5 / 86;  half full, 4000 x 24
-  // 200 / 199, 2000 x 24 x 2 108 / 111, 900 x 24 x 4 60 / 57;  4352 x 24 225 / 223, 5120 x 24 281 / 264) or a third one a quarter full
-  // (6000 x 24 405 / 421, 2000 x 24 x 3 150 / 158, 700 x 24 x 8 64 / 67;  16384 x 10, half full, 1114 / 1108).
+  // Else, at D 128, the ping-pong kernel (7 to 25 % ahead from 1.75 items per compute unit on: 4608 x 24 253 / 244, 5120 x 24 328 /
+  // 279, 8000 x 16 515 / 425, 20506 x 6 1270 / 1062, 1024 x 24 x 8 118 / 106, 6000 and 3000 x 17 347 / 314), but for
+  // cross-attention items of up to eleven key tiles (see above) and items that leave much of its last round empty.
   // (Comparisons of two kernels must be made on a warm chip: in the first ~20 ms after idle, while the clocks still
   // ramp, whichever kernel runs second looks faster.)
   if (cu_seqlens_k != nullptr && tiles <= 11 * items256) return AttnKernel::kIndependent128;
-  if (items256 > n_cus && 7 * (items256 - n_cus) <= 3 * (int64_t)n_cus) return AttnKernel::kIndependent128;
-  if (items256 > 2 * (int64_t)n_cus && 4 * (items256 - 2 * (int64_t)n_cus) <= (int64_t)n_cus && tiles == max_tiles * items256)
+  // One round of the 128-row kernel against two: 1100 x 14 x 4 45.0 / 53.4, 300 x 14 x 10 16.9 / 23.4.
+  if (items128 <= 2 * (int64_t)n_cus) return AttnKernel::kIndependent128;
+  // A second round at most half full: 4096 x 22 170 / 190, x 24 176 / 211, 4000 x 24 178 / 197, 8000 x 12 334 / 404, 3841 x 23 161 /
+  // 178, 2000 x 24 x 2 98 / 114, 1280 x 15 x 5 67 / 75, 1281 x 21 x 3 65 / 76, 8192, 300 and 77 x 12 350 / 418, 2458 and 1054 x 13 x
+  // 2 98 / 114, against 1000 keys 4000 x 24 53 / 63;  past it 4352 x 24 234 / 230, 4352 x 26 243 / 233, 3000 x 36 170 / 166, 1500 x 22 x
+  // 3 90 / 89, 8704 x 15 against 1000 keys 69.2 / 66.8.
+  // Not self-attention of 12 to 18 key tiles: 1024 x 18 x 4 60.2 / 56.0, x 24 66.5 / 62.6, 900 x 20 x 4 55.5 / 52.3, 1100 x 19 x 4
+  // 68.2 / 65.9, 1152 x 18 x 4 66.4 / 62.9, 800 x 16 x 6 50.7 / 47.8 (why sequences of about a
+  // thousand rows take the 128-row kernel so long there is not known, 1280 x 19 x 4 is 67.1 / 75.6).  And with fewer tiles, where
+  // either can be ahead, at most three sevenths full: 300 x 16 x 10 18.7 / 22.9, 410 x 16 x 10 29.7 / 31.4, 256 x 15 x 20 23.5 / 25.7,
+  // 700 x 12 x 8 39.7 / 42.5, 512 x 16 x 9 35.9 / 36.1, 512 x 13 x 14 40.7 / 38.6, 640 x 13 x 9 42.6 / 38.6;  past it 410 x 16 x 12
+  // 34.9 / 32.0, 512 x 16 x 12 41.5 / 38.2.
+  const int64_t second = items256 - n_cus, third = items256 - 2 * (int64_t)n_cus;  // 256-row items of a round and later ones
+  if (second > 0 && (tiles <= 11 * items256 ? 7 * second <= 3 * (int64_t)n_cus
+                                            : 2 * second <= n_cus && (cu_seqlens_k != nullptr || tiles > 18 * items256)))
     return AttnKernel::kIndependent128;
+  // A third round of equal items at most half full: 6000 x 24 387 / 413, 4096 x 33 264 / 278, x 40 298 / 317, 16384 x 10 1152 / 1202,
+  // 2000 x 20 x 4 154 / 159, 1024 x 16 x 9 88 / 92, 700 x 24 x 8 63.4 / 65.9, 1000 x 16 x 10 90.5 / 90.9;  past it 2000 x 28 x 3 174 /
+  // 171, 700 x 24 x 10 81 / 77, 6000 x 32 515 / 491, 16384 x 12 1389 / 1332.
+  if (third > 0 && 2 * third <= n_cus && tiles == max_tiles * items256) return AttnKernel::kIndependent128;
   return AttnKernel::kPingPong256;
 }
 

@@ -139,13 +139,13 @@ def test_bench_refuses_more_than_one_gpu():
 def test_kernel_choice_by_items_per_compute_unit():
     """dit_attn_plan's block_m shows which kernel family a pack gets on a 256-CU device: the 128-row kernel while each of its
     items has a compute unit of its own (8 heads: 65 us, the ping-pong kernel 80) and for packs whose second round of 256-row
-    items would be at most three sevenths or a third one a quarter full, the 256-row (ping-pong) kernel otherwise.  4096 tokens
-    are 32 items of 128 rows per head, 16 of 256."""
+    items or third one of equal items would be at most half full (24 heads: 176 us, the ping-pong kernel 211; 40 heads 298, 317),
+    the 256-row (ping-pong) kernel otherwise.  4096 tokens are 32 items of 128 rows per head, 16 of 256."""
     def block_m(lens, heads):
         cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
         return da.dit_attn_plan(cu, heads, 128)[1]
-    expect = {6: 128, 7: 128, 8: 128, 9: 256, 10: 256, 12: 256, 16: 256, 17: 128, 20: 128, 22: 128, 23: 256, 24: 256, 25: 256,
-              32: 256, 40: 256, 41: 256, 48: 256, 49: 256, 64: 256}
+    expect = {6: 128, 7: 128, 8: 128, 9: 256, 10: 256, 12: 256, 16: 256, 17: 128, 20: 128, 22: 128, 23: 128, 24: 128, 25: 256,
+              32: 256, 40: 128, 41: 256, 48: 256, 49: 256, 64: 256}
     for heads, bm in expect.items():
         assert block_m([4096], heads) == bm, heads
     assert block_m([20506], 24) == 256

@@ -72,9 +72,19 @@ def test_cross_choice_at_head_dim_64(n_keys, kernel):
     ([2100], 15, 128, 128),          # 255, although 135 items of 256 rows are more than half of the compute units
     ([200] * 16, 8, 128, 128),       # 256 ragged ones
     ([3600], 24, 128, 128),          # 360: a second round 41 % full
-    ([3841], 23, 128, 256),          # 368: 44 %
+    ([3841], 23, 128, 128),          # 368, 44 %: 161 us, the ping-pong kernel 178
+    ([4096], 24, 128, 128),          # 384: half full
+    ([4097], 23, 128, 256),          # 391
+    ([1152] * 4, 19, 128, 256),      # 380 items of 18 key tiles
+    ([1153] * 4, 19, 128, 128),      # 19
+    ([1152] * 4, 14, 128, 128),      # 504 items of 128 rows: one round of two on every compute unit
+    ([700] * 10, 12, 128, 128),      # 360 of 11 key tiles: at most three sevenths
+    ([700] * 10, 13, 128, 256),      # 390
+    ([705] * 10, 12, 128, 256),      # 12
     ([6000], 24, 128, 128),          # 576 equal items: a third round a quarter full
-    ([6000], 25, 128, 256),          # 600
+    ([6000], 25, 128, 128),          # 600: 413 us, the ping-pong kernel 431
+    ([4096], 40, 128, 128),          # 640: half full
+    ([4097], 38, 128, 256),          # 646
     ([6000, 3000], 17, 128, 256),    # 612 items of two lengths: the short ones fill the round
     ([8128], 24, 64, 128),           # 127 key tiles: 395 us, the ping-pong kernel 416
     ([8129], 24, 64, 128),           # 128
