@@ -232,13 +232,15 @@ int dit_attn_set_kernel(dit_attn_ctx* ctx, int kernel);
 /*
  * Split-KV for small packs (paper Section 3 / Table 3: a low-resolution image step is far too small to fill a GPU).
  * With max_splits > 1, a pack whose work items leave at least half of the compute units idle has the keys of every
- * sequence cut into up to max_splits chunks: as many as fit one round of one item per compute unit, at most one per eight
- * tiles of 64 keys of the shortest sequence, and only where that takes at least 12 such tiles off every item of the 128-row
- * kernel (sequences under 32 tiles) or 17 of the ping-pong kernel, which is what the partial results and their merge cost
- * on MI355X.  The chunks of a sequence have equal numbers of tiles but for the last, which takes what is left (65 tiles in
- * eight chunks: seven of 9 tiles and one of 2).  They run as separate items that leave normalised fp32 partial results and
- * their log-sum-exp in a workspace owned by the context (grown with hipMalloc when a call needs more), and one merge kernel
- * on the same stream writes `out`.  Off (max_splits = 1) by default, because it changes the summation order: with it
+ * sequence cut into up to max_splits chunks: as many as fit one round of one item per compute unit and at most one per eight
+ * tiles of 64 keys of the shortest sequence, where that is quicker on MI355X than the unsplit call.  Where two 128-row items
+ * per compute unit fit, the chunks run on the 128-row kernel if the shortest sequence has under 64 tiles and the split takes
+ * at least 12 of them (head_dim 64: 13) off every item, else on the ping-pong kernel, where it has to take 17.  Without that
+ * room a pack is split only if its longest sequence has 128 tiles, on the ping-pong kernel.  (The partial results and their
+ * merge cost about 8 us.)  The chunks of a sequence have equal numbers of tiles but for the last, which takes what is left
+ * (65 tiles in eight chunks: seven of 9 tiles and one of 2).  They run as separate items that leave normalised fp32 partial
+ * results and their log-sum-exp in a workspace owned by the context (grown with hipMalloc when a call needs more), and one
+ * merge kernel on the same stream writes `out`.  Off (max_splits = 1) by default, because it changes the summation order: with it
  * a sequence's bits depend on what it is packed with (they stay within the same tolerance of the exact result).
  * Applies to every forward entry point.  Returns DIT_ATTN_OK, DIT_ATTN_ERR_NULL or DIT_ATTN_ERR_PARTS (outside 1..8).
  */

@@ -252,45 +252,50 @@ namespace {
 // Split-KV (opt-in): a pack that leaves compute units idle cuts every sequence's keys into chunks, as many as still run in
 // one round, one workgroup per compute unit, and at most one per eight key tiles of the shortest sequence, and merges the
 // parts.  (A sequence's chunks have equal numbers of key tiles but for the last, which takes what is left.)
-// Measured on MI355X, head dimension 128 unless noted, rows x heads: us unsplit / ping-pong kernel (2, 3, 4, 5, 8 chunks) /
-// 128-row kernel (the same):
-//   16384 x 1          284 / 167 131 124 165 134 / 165 161 138 161 147
-//   10000 x 3          183 / 138 172 155 173 176 / 158 170 171 169 193
-//   8192 x 2           145 /  90  74  71  93  84 /  88  86  78  90  88
-//   4951 x 3            88 /  61  50  48  66  62 /  57  57  52  61  63
-//   4096 x 6            80 /  60  83  75  75  87 /  71  78  70  77  89
-//   4096 x 4, D 64      53 /  42  33  34  42  40 /  37  35  34  37  38
-//   3 of 2000, 2 heads  39 /  33  30  28  34  40 /  30  32  30  32  37
-//   2500 x 3            47 /  37  30  30  26  28 /  33  27  27  28  28
-//   1570 x 5            31 /  29  26  27  24  27 /  25  22  24  25  28
-// The ping-pong kernel is ahead where a chunk count fills one round of its items, also with queries of less than 128 rows a
-// sequence (4 of 128 x 24 against 4096 keys each unsplit 72 / 45 / 47, 77 x 24 against 20506 keys 347 / 50 / 55, 3 of 100 x 24
-// against 4352, D 64, 55 / 25 / 26);  with under 32 key tiles the shorter items of the 128-row kernel are.
-// (That sweep was made with kernels whose unsplit times have fallen since, 4951 x 3 to 60 us, and whose fp32 partials were
-// stored in pieces: 4951 x 3 in four chunks takes 46.5 us now.)
-// The partial results and their merge cost about 8 us, a key tile 1 us per item of the ping-pong kernel at head dimension 128
-// and less elsewhere.  What a split has to take off every item, unsplit / split in two, at D 128 and D 64:
-//   12 tiles, 128-row kernel    1536 x 10 30.9 / 27.1, 22.4 / 20.2
-//   16 tiles, ping-pong kernel  2048 x 14 41.1 / 42.6, 28.7 / 28.9;  x 16 44.3 / 46.4, 29.4 / 31.0;  x 12 40.2 / 39.8, 28.6 / 27.9
-//   18 tiles                    2304 x 14 48.3 / 49.4, 32.4 / 32.7       20 tiles  2560 x 12 52.3 / 50.8, 35.1 / 34.1
-// With the 128-row kernel forced and more than half of the compute units busy a split gains nothing (4352 x 4 77 / 80).
-void choose_split(const dit_attn_ctx* ctx, const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads,
+// Measured on MI355X in random order, rows x heads: us unsplit / 128-row kernel / ping-pong kernel, each in as many chunks as the
+// rule gives it (in brackets; -: it makes none).
+//   Room for two 128-row items per compute unit and under 64 key tiles: the 128-row kernel.
+//     D 128  1570 x 5 23.3 / 17.9 (3) / 23.8 (3), 2048 x 8 28.2 / 26.8 (2) / 29.7 (4), 2048 x 4 27.3 / 23.9 (4) / 26.6 (4),
+//            2500 x 3 33.0 / 23.6 (4) / 24.1 (5), 2500 x 6 34.1 / 28.8 (2) / 32.3 (4), 3500 x 4 44.7 / 33.9 (2) / 35.9 (4)
+//     D 64   2048 x 8 20.2 / 18.8 / 23.3, 2048 x 4 19.5 / 15.5 / 18.9, 2500 x 3 23.7 / 15.7 / 19.4, 2500 x 6 24.2 / 20.7 / 24.6
+//   The same room and more tiles, where the ping-pong kernel makes more chunks: either can be ahead, the ping-pong kernel as they
+//   get long.
+//     D 128  4096 x 4 50.0 / 41.1 (2) / 43.2 (4), 4951 x 3 60.1 / 45.4 (2) / 47.2 (4), 5600 x 2 65.1 / 42.4 (2) / 40.1 (5),
+//            6000 x 1 68.7 / 28.6 (5) / 33.1 (8), 8192 x 2 94.5 / 71.7 (2) / 70.6 (4), 12000 x 1 134 / 81 (2) / 72.5 (5),
+//            16384 x 1 189 / 133 (2) / 126 (4);  300 x 24 against 6000 keys 71.2 / 39.8 (3) / 36.8 (5), 77 x 24 against 20506 keys
+//            228 / 53.5 (8) / 52.8 (8)
+//     D 64   4951 x 3 42.8 / 30.7 / 33.3, 6000 x 2 50.1 / 32.6 / 29.6, 12000 x 1 97 / 56 / 47, 16384 x 1 133 / 83 / 81
+//   Without that room the unsplit items of the 128-row kernel leave few compute units idle: only where the longest have 128
+//   tiles.
+//     D 128  2304 x 14 39.5 / - / 46.4 (2), 2560 x 12 41.8 / - / 47.9 (2), 3584 x 8 54.1 / - / 58.1 (2), 4096 x 6 56.0 / - / 58.0 (2),
+//            6000 x 5 90.3 / - / 92.3 (2), 7000 x 4 95.9 / - / 95.0 (2), 8192 x 3 101.5 / - / 98.0 (2), 10000 x 3 147 / - / 142 (2),
+//            16384 x 2 238 / - / 222 (2), 20506 x 1 237 / - / 181 (3), 6200, 6147 and 10000 x 1 118 / - / 108 (2)
+//     D 64   2304 x 14 25.1 / - / 29.7, 3584 x 8 34.6 / - / 37.3, 6000 x 5 57.2 / - / 58.3, 8192 x 4 79.7 / - / 78.5, 20506 x 1 168 / - / 120
+// The partial results and their merge cost about 8 us.  Tiles that a split on the 128-row kernel has to take off every item:
+//   12 at D 128  1536 x 10 23.1 / 22.7, 1600 x 9 23.2 / 21.9;   13 at D 64  1536 x 10 16.1 / 16.5, 1664 x 9 17.0 / 16.9;  10 at either
+//   1280 x 8 19.6 / 18.9 and 13.6 / 13.9
+// (A forced kernel is split by its own items, and the ping-pong kernel for 17 tiles or more.)
+void choose_split(const dit_attn_ctx* ctx, const int32_t* cu_q, const int32_t* cu_k, int32_t n_seqs, int32_t n_heads, int32_t head_dim,
                   dit::AttnKernel* kernel, int32_t* n_splits) {
-  int64_t rows128 = 0, rows256 = 0, min_tiles = INT64_MAX;  // query tiles of either height
+  int64_t items128 = 0, items256 = 0, min_tiles = INT64_MAX, max_tiles = 0;  // unsplit items of either height; key tiles
   for (int32_t i = 0; i < n_seqs; ++i) {
     const int64_t lq = cu_q[i + 1] - cu_q[i], lk = cu_k[i + 1] - cu_k[i];
     if (lq == 0 || lk == 0) continue;
-    rows128 += (lq + 127) / 128;
-    rows256 += (lq + 255) / 256;
+    items128 += (lq + 127) / 128 * n_heads;
+    items256 += (lq + 255) / 256 * n_heads;
     min_tiles = std::min<int64_t>(min_tiles, (lk + 63) / 64);
+    max_tiles = std::max<int64_t>(max_tiles, (lk + 63) / 64);
   }
-  if (rows128 == 0) return;
-  const dit::AttnKernel split_kernel = ctx->force_kernel >= 0 ? *kernel
-                                       : min_tiles < 32       ? dit::AttnKernel::kIndependent128
-                                                              : dit::AttnKernel::kPingPong256;
-  const int64_t items = (split_kernel == dit::AttnKernel::kIndependent128 ? rows128 : rows256) * n_heads;
-  const int64_t n = std::min<int64_t>({ctx->n_cus / items, ctx->max_splits, min_tiles / 8});
-  if (n < 2 || min_tiles - (min_tiles + n - 1) / n < (split_kernel == dit::AttnKernel::kIndependent128 ? 12 : 17)) return;
+  if (items128 == 0) return;
+  dit::AttnKernel split_kernel = *kernel;
+  if (ctx->force_kernel < 0) {
+    const bool room = 2 * items128 <= ctx->n_cus;
+    if (!room && max_tiles < 128) return;
+    split_kernel = room && min_tiles < 64 ? dit::AttnKernel::kIndependent128 : dit::AttnKernel::kPingPong256;
+  }
+  const bool rows128 = split_kernel == dit::AttnKernel::kIndependent128;
+  const int64_t n = std::min<int64_t>({ctx->n_cus / (rows128 ? items128 : items256), ctx->max_splits, min_tiles / 8});
+  if (n < 2 || min_tiles - (min_tiles + n - 1) / n < (!rows128 ? 17 : head_dim == 64 ? 13 : 12)) return;
   *kernel = split_kernel;
   *n_splits = static_cast<int32_t>(n);
 }
@@ -331,7 +336,7 @@ int forward(dit_attn_ctx* ctx, const void* q, const void* k, const void* v, cons
   dit::AttnKernel kernel = ctx->force_kernel >= 0 ? static_cast<dit::AttnKernel>(ctx->force_kernel)
                                                   : dit::attn_fwd_select(cu_seqlens, cu_k, n_seqs, n_heads, head_dim, ctx->n_cus);
   int32_t n_splits = 1;
-  if (ctx->max_splits > 1) choose_split(ctx, cu_seqlens, cu_k ? cu_k : cu_seqlens, n_seqs, n_heads, &kernel, &n_splits);
+  if (ctx->max_splits > 1) choose_split(ctx, cu_seqlens, cu_k ? cu_k : cu_seqlens, n_seqs, n_heads, head_dim, &kernel, &n_splits);
   for (auto& p : ctx->plans) {
     if (p->n_heads == n_heads && p->head_dim == head_dim && p->kernel == kernel && p->n_splits == n_splits && p->cu.size() == cu_n &&
         p->cu_k.size() == (cu_k ? cu_n : 0) && std::memcmp(p->cu.data(), cu_seqlens, cu_n * sizeof(int32_t)) == 0 &&

@@ -1,6 +1,6 @@
-"""Split keys where the choice of kernel and of the number of chunks changes: 31 and 32 key tiles, a pack whose chunks fill
-the compute units exactly and one that no longer splits, the fewest tiles that a split has to take off an item, a short last
-chunk; both head dimensions, ragged lengths.  The number of chunks and the kernel are checked, and two calls' bits."""
+"""Split keys where the choice of kernel and of the number of chunks changes: 63 and 64, 127 and 128 key tiles, packs whose
+chunks fill the compute units exactly and ones that no longer split, the fewest tiles that a split has to take off an item, a
+short last chunk; both head dimensions, ragged lengths.  The number of chunks and the kernel are checked, and two calls' bits."""
 import pytest
 import torch
 
@@ -26,13 +26,22 @@ def _exact(q, k, v, cu, scale):
 @pytest.mark.parametrize("lens,H,D,max_splits,chunks,kernel", [
     ([4951], 3, 128, 8, 4, da.KERNEL_PINGPONG),         # 60 items of 256 rows: four chunks in one round
     ([1984], 3, 128, 8, 3, da.KERNEL_128),              # 31 key tiles
-    ([1985], 3, 64, 8, 4, da.KERNEL_PINGPONG),          # 32 key tiles, the last chunk 63 keys shorter than the others
-    ([8192, 8129], 2, 64, 2, 2, da.KERNEL_PINGPONG),    # 128 items of 256 rows: two chunks fill 256 compute units
-    ([8193, 8192], 2, 128, 8, 1, None),                 # 130 items: no split
+    ([1985], 3, 64, 8, 4, da.KERNEL_128),               # 32 key tiles, the last chunk 63 keys shorter than the others
+    ([4032], 3, 128, 8, 2, da.KERNEL_128),              # 63 tiles, 96 items of 128 rows: two chunks in one round
+    ([4033], 3, 128, 8, 5, da.KERNEL_PINGPONG),         # 64 tiles, 48 items of 256 rows
+    ([2048], 8, 64, 8, 2, da.KERNEL_128),               # 128 items of 128 rows, two for every compute unit
+    ([2049], 8, 64, 8, 1, None),                        # 136: no room for another round of them
+    ([8192, 8129], 2, 64, 2, 2, da.KERNEL_PINGPONG),    # 256 of them, 128 tiles: two chunks fill 256 compute units
+    ([8128, 8127], 2, 64, 8, 1, None),                  # 127 tiles
+    ([8193, 8192], 2, 128, 8, 1, None),                 # 130 items of 256 rows: no split
     ([1535], 2, 128, 8, 3, da.KERNEL_128),              # 24 tiles: three chunks of eight
     ([1472], 2, 128, 2, 1, None),                       # 23 tiles: two chunks take eleven tiles off an item, too few
-    ([2112], 14, 64, 8, 1, None),                       # 33 tiles, 126 items of 256 rows: two chunks would take sixteen off
-    ([2176], 14, 64, 8, 2, da.KERNEL_PINGPONG),         # 34 tiles: seventeen
+    ([1536], 5, 128, 2, 2, da.KERNEL_128),              # 24: twelve
+    ([1536], 5, 64, 2, 1, None),                        # which are too few at head dimension 64
+    ([1601], 5, 64, 2, 2, da.KERNEL_128),               # 26: thirteen
+    ([2112], 14, 64, 8, 1, None),
+    ([2176], 14, 64, 8, 1, None),                       # 238 items of 128 rows: 23.3 us, two chunks of 256-row items 27.8
+    ([2304], 14, 128, 8, 1, None),                      # 39.5 us and 46.4
     ([4160, 4480], 1, 128, 8, 7, da.KERNEL_PINGPONG),   # 35 items; 65 tiles in seven chunks: 10 each, the last 5
 ])
 def test_split_choice(lens, H, D, max_splits, chunks, kernel):
