@@ -685,9 +685,6 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)"
 // Waits until at most N of this wavefront's vector-memory operations (the youngest N) are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// Workgroup barrier that does not wait for this wave's outstanding LDS reads: for a point where the buffers those
-// reads address are not written by anyone before the next barrier.
-__device__ __forceinline__ void phase_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // Work distribution: workgroup b starts with list index b; further indices come from one atomic counter (thread 0
 // of a workgroup), offset by the grid size; indices at or past n_items end the workgroup.  A workgroup asks for its

@@ -12,10 +12,11 @@ namespace dit {
 // three back to back the two pipes of a SIMD took turns unless another wavefront happened to be at the right place: a
 // wavefront alone on its SIMD used each of them a third of the time.  Alone it is bound by its own instruction issue (about
 // five cycles each, 195 instructions a tile at head dimension 64), which is why the main loop has neither address
-// arithmetic (slots of the K / V rings are immediate offsets, the loads run on pointers) nor tests.  MI355X, us, back to
-// back / as it is: 1024 rows x 8 heads, D 64 15.7 / 12.5;  16384 x 1, D 64 199 / 136;  410 x 24, D 64 8.7 / 7.8;  image
-// batch, D 64 (410 to 4250 rows x 24) 352 / 330;  9000 x 24, D 64 545 / 493;  1024 x 8, D 128 22.1 / 19.1;  4951 x 3,
-// D 128 88.5 / 69.6.
+// arithmetic (slots of the K / V rings are immediate offsets, the loads run on pointers) nor tests.  MI355X, us, the kernel
+// with the three back to back / this one: 1024 rows x 8 heads, D 64 15.7 / 11.7;  16384 x 1, D 64 199 / 133;  410 x 24, D 64
+// 8.7 / 7.5;  image batch, D 64 (410 to 4250 rows x 24) 349 / 327;  9000 x 24, D 64 545 / 497;  1024 x 8, D 128 22.1 / 17.0;
+// 4951 x 3, D 128 88.7 / 60.6;  3600 x 24, D 128 170 / 154.  (Slower: cross-attention at D 64 in two rounds of six to eight
+// tiles, 7912 x 24 against 357 keys 30.2 / 31.8, 400 keys 32.2 to 33.7 / 33.9 to 35.4, 500 keys 36.8 to 38.8 / 37.9 to 39.5.)
 //
 // Two K and V ring slots let several workgroups share a compute unit: three at head dimension 64, two at 128 (a third
 // wavefront per SIMD at 64, in 159 registers, fills more of the issue slots: image batch 344 with two, 332 with three).
@@ -641,11 +642,12 @@ static hipError_t launch_p(const P& p, AttnKernel kernel, int head_dim, int n_cu
     if (head_dim == 64) return launch_t<TilePP64, P, attn_fwd_pp_kernel<TilePP64, P>>(p, grid, stream);
   } else {
     // Where no compute unit has two items, D 128, us with two slots and a step's loads spread / at its start / with four slots:
-    //   at most half of the compute units busy  448 x 8 9.4 / 10.0 / 10.3,  832 x 8 13.7 / 14.9 / 14.3,  1024 x 8 17.2 / 17.9 /
-    //     17.0,  1280 x 10 20.6 / 21.3 / 20.0,  2048 x 3 26.9 / 30.1 / 27.0,  4096 x 4 51.2 / 56.8 / 50.2: four from 16 tiles on;
-    //   more of them  448 x 40 10.9 / 11.0 / 12.0,  700 x 24 14.7 / 14.8 / 15.7,  900 x 24 19.4 / 18.8 / 20.2,  1024 x 24 21.5 /
-    //     20.4 / 21.7,  1152 x 24 23.3 / 22.8 / 24.4,  1280 x 24 25.4 / 25.3 / 26.4,  1792 x 17 30.8 / 32.5 / 31.3,  3584 x 8 52.2 /
-    //     55.7 / 52.3: the loads at the start between 12 and 19 tiles (why is not known).
+    //   at most half of the compute units busy  448 x 8 9.5 / 10.1 / 10.5,  832 x 8 13.7 / 15.1 / 14.4,  1024 x 8 17.3 / 18.1 /
+    //     17.1,  1280 x 10 20.6 / 21.5 / 20.1,  1536 x 10 23.6 / 24.8 / 22.9,  2048 x 8 29.4 / 31.4 / 28.4,  2048 x 3 27.1 / 30.3 /
+    //     27.2,  4096 x 4 51.1 / 57.5 / 50.6: four from 16 tiles on, up to 4 % ahead;
+    //   more of them  448 x 40 11.0 / 11.3 / 12.3,  700 x 24 14.7 / 15.0 / 15.7,  900 x 24 19.3 / 18.9 / 20.6,  1024 x 20 19.7 / 19.3 /
+    //     19.5,  1024 x 24 21.2 / 20.8 / 21.6,  1152 x 24 23.2 / 23.4 / 24.2,  1280 x 24 25.7 / 26.4 / 26.0,  1792 x 17 32.0 / 33.7 /
+    //     32.0,  3584 x 8 53.2 / 56.6 / 53.2: the loads at the start between 12 and 19 tiles, 2 % ahead (why is not known).
     if (head_dim == 128 && p.n_items <= (uint32_t)n_cus) {
       const bool half = 2 * p.n_items <= (uint32_t)n_cus;
       if (half && max_keys > 64 * 15) return launch_t<Tile128Deep, P, attn_fwd_kernel<Tile128Deep, P>>(p, grid, stream);
